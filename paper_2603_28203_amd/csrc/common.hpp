@@ -101,6 +101,32 @@ __device__ __forceinline__ double wave_max(double v) {
     for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
     return v;
 }
+// The same reductions where one lane suffices: partial results move up the lanes
+// with DPP moves (row shifts within 16 lanes, then the two row broadcasts), about
+// 6 x 20 cycles against 6 x 100 for the butterfly through the LDS crossbar, and the
+// last lane holds the result.  the maximum takes values >= 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double x) {
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffLL), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+__device__ __forceinline__ void wave_last_sum_max(double &s, double &m) {
+    constexpr int kShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143;
+    s += dpp_or_zero<kShr + 1, 0xf>(s);
+    m = fmax(m, dpp_or_zero<kShr + 1, 0xf>(m));
+    s += dpp_or_zero<kShr + 2, 0xf>(s);
+    m = fmax(m, dpp_or_zero<kShr + 2, 0xf>(m));
+    s += dpp_or_zero<kShr + 4, 0xf>(s);
+    m = fmax(m, dpp_or_zero<kShr + 4, 0xf>(m));
+    s += dpp_or_zero<kShr + 8, 0xf>(s);
+    m = fmax(m, dpp_or_zero<kShr + 8, 0xf>(m));
+    s += dpp_or_zero<kBcast15, 0xa>(s);
+    m = fmax(m, dpp_or_zero<kBcast15, 0xa>(m));
+    s += dpp_or_zero<kBcast31, 0xc>(s);
+    m = fmax(m, dpp_or_zero<kBcast31, 0xc>(m));
+}
 // A value that every lane of the wave holds identically, moved to scalar
 // registers: lets the compiler treat what depends on it as uniform.
 __device__ __forceinline__ double uniform(double x) {
@@ -176,23 +202,50 @@ __device__ __forceinline__ void branch_admittance(double r, double x, double b, 
 }
 
 // ---------------------------------------------------------------- optimizer
-// One optimizer update of a learnable coordinate x with gradient g and state
-// m (first moment / momentum buffer), s (second moment); kind = DPF_OPT_*
-// (0 Adam with bias corrections bc1 = 1 - b1^t, bc2 = 1 - b2^t; 1 SGD with
-// momentum b1; 2 RMSprop with smoothing b2).
-__device__ __forceinline__ double opt_update(int kind, double lr, double b1, double b2, double eps, double bc1,
-                                             double bc2, double x, double g, double &m, double &s) {
-    if (kind == 1) {
-        m = b1 * m + g;
-        return x - lr * m;
+// What one optimizer update needs beside a coordinate's own values, the same for
+// every bus of an item and iteration: kind = DPF_OPT_* (0 Adam with bias
+// corrections bc1 = 1 - b1^t, bc2 = 1 - b2^t; 1 SGD with momentum b1; 2 RMSprop
+// with smoothing b2).  Adam's two bias corrections are folded into the rate and
+// into one factor per iteration, so that a coordinate pays one division and one
+// square root (each about 10 to 15 FP64 instructions on gfx950, a third of all the
+// arithmetic of a bus-iteration when the corrections were divisions of their own).
+struct OptStep {
+    int kind;
+    double b1, b2, eps;
+    double rate;  // lr; Adam: lr / bc1
+    double q2;    // Adam: 1 / bc2
+};
+__device__ __forceinline__ OptStep opt_step(int kind, double lr, double b1, double b2, double eps, double bc1,
+                                            double bc2) {
+    OptStep o{kind, b1, b2, eps, lr, 1.0};
+    if (kind == 0) {
+        o.rate = lr / bc1;
+        o.q2 = 1.0 / bc2;
     }
-    if (kind == 2) {
-        s = b2 * s + (1.0 - b2) * (g * g);
-        return x - lr * (g / (sqrt(s) + eps));
+    return o;
+}
+
+// One update of a learnable coordinate x with gradient g and state m (first
+// moment / momentum buffer), s (second moment).
+__device__ __forceinline__ double opt_update(const OptStep &o, double x, double g, double &m, double &s) {
+    if (o.kind == 1) {
+        m = o.b1 * m + g;
+        return x - o.rate * m;
     }
-    m = b1 * m + (1.0 - b1) * g;
-    s = b2 * s + (1.0 - b2) * (g * g);
-    return x - lr * (m / bc1) / (sqrt(s / bc2) + eps);
+    if (o.kind == 2) {
+        s = o.b2 * s + (1.0 - o.b2) * (g * g);
+        return x - o.rate * (g / (sqrt(s) + o.eps));
+    }
+    m = o.b1 * m + (1.0 - o.b1) * g;
+    s = o.b2 * s + (1.0 - o.b2) * (g * g);
+    return x - o.rate * (m / (sqrt(s * o.q2) + o.eps));
+}
+
+// d loss / d|V| = Re(conj(G) V) / |V| with V = vm (cs + j sn): the division cancels,
+// except that a magnitude of exactly zero has no direction (0 / 0, NaN)
+__device__ __forceinline__ double grad_vm(double2 G, double cs, double sn, double vm) {
+    const double g = G.x * cs + G.y * sn;
+    return vm == 0.0 ? __longlong_as_double(0x7ff8000000000000LL) : g;
 }
 
 // ---------------------------------------------------------------- sin / cos
@@ -315,17 +368,36 @@ __device__ __forceinline__ double kcos(double x, double y) {
     return a - (hz - (z * r - x * y));
 }
 
+// sin and cos for |x| <= pi/4, the range of nearly every bus angle: the same
+// polynomials with no reduction tail and no quadrant, and 1 - x^2/2 carried with
+// its rounding error instead of a case distinction on |x|
+__device__ __forceinline__ void near_sincos(double x, double &s, double &c) {
+    const double S1 = -1.66666666666666324348e-01, S2 = 8.33333333332248946124e-03,
+                 S3 = -1.98412698298579493134e-04, S4 = 2.75573137070700676789e-06,
+                 S5 = -2.50507602534068634195e-08, S6 = 1.58969099521155010221e-10;
+    const double C1 = 4.16666666666666019037e-02, C2 = -1.38888888888741095749e-03,
+                 C3 = 2.48015872894767294178e-05, C4 = -2.75573143513906633035e-07,
+                 C5 = 2.08757232129817482790e-09, C6 = -1.13596475577881948265e-11;
+    const double z = x * x;
+    const double rs = S2 + z * (S3 + z * (S4 + z * (S5 + z * S6)));
+    const double rc = C1 + z * (C2 + z * (C3 + z * (C4 + z * (C5 + z * C6))));
+    s = x + (z * x) * (S1 + z * rs);
+    const double h = 0.5 * z, w = 1.0 - h;
+    c = w + (((1.0 - w) - h) + (z * z) * rc);
+}
+
 __device__ __forceinline__ void fast_sincos(double x, double &s, double &c) {
+    if (fabs(x) <= 0.785398163397448279) {
+        near_sincos(x, s, c);
+        return;
+    }
     const double invpio2 = 6.36619772367581382433e-01;
     const double p1 = 1.57079632673412561417e+00, p2 = 6.07710050630396597660e-11,
                  p2t = 2.02226624879595063154e-21, p3 = 2.02226624871116645580e-21,
                  p3t = 8.47842766036889956997e-32;
     double y0, y1;
     int n = 0;
-    if (fabs(x) <= 0.785398163397448279) {
-        y0 = x;
-        y1 = 0.0;
-    } else if (!(fabs(x) <= 823550.0)) {  // 2^19 pi/2, also catches NaN and Inf
+    if (!(fabs(x) <= 823550.0)) {  // 2^19 pi/2, also catches NaN and Inf
         if (fabs(x) <= 1.79769313486231570815e+308) {
             n = reduce_payne_hanek(x, y0, y1);
         } else {

@@ -204,8 +204,7 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
         sc.t_step += 1.0;
         sc.b1t *= a.b1;
         sc.b2t *= a.b2;
-        const double bc1 = 1.0 - sc.b1t;
-        const double bc2 = 1.0 - sc.b2t;
+        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
         for (int s = 0; s < nb; ++s) {
 #pragma unroll
             for (int j = 0; j < J; ++j) {
@@ -225,12 +224,9 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                     if (il == of) h = csub(h, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
                     else if (il == ot) h = csub(h, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
                     double vmi = p0.x, vai = p0.y;
-                    double2 v;
-                    {
-                        double sn0, cs0;
-                        fast_sincos(vai, sn0, cs0);
-                        v = make_double2(vmi * cs0, vmi * sn0);
-                    }
+                    double sn0, cs0;
+                    fast_sincos(vai, sn0, cs0);
+                    const double2 v = make_double2(vmi * cs0, vmi * sn0);
                     // the seed of the A/W sweep, rebuilt from I and the same V
                     const double2 d = csub(cmulc(v, I), sp);
                     const double rP = tk != kSlack ? d.x : 0.0;
@@ -239,12 +235,12 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                     const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
                     double mv = p1.x, ma = p1.y, sv = p2.x, sa = p2.y;
                     if (tk == kPQ) {
-                        const double g = (G.x * v.x + G.y * v.y) / vmi;
-                        vmi = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vmi, g, mv, sv);
+                        const double g = grad_vm(G, cs0, sn0, vmi);
+                        vmi = opt_update(os, vmi, g, mv, sv);
                     }
                     if (tk != kSlack) {
                         const double g = G.y * v.x - G.x * v.y;
-                        vai = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vai, g, ma, sa);
+                        vai = opt_update(os, vai, g, ma, sa);
                         P0[i] = make_double2(vmi, vai);
                         P1[i] = make_double2(mv, ma);
                         P2[i] = make_double2(sv, sa);

@@ -97,10 +97,9 @@ struct SolveArgs {
 
 template <int NT>
 __device__ __forceinline__ void block_reduce2(double &s, double &m, double (*red)[NT / kWave]) {
-    s = wave_sum(s);
-    m = wave_max(m);
+    wave_last_sum_max(s, m);
     const int wv = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) {
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) {
         red[0][wv] = s;
         red[1][wv] = m;
     }
@@ -429,8 +428,7 @@ __global__ __launch_bounds__(NT) void team_solve_kernel(SolveArgs a) {
         sc.t_step += 1.0;
         sc.b1t *= a.b1;
         sc.b2t *= a.b2;
-        const double bc1 = 1.0 - sc.b1t;
-        const double bc2 = 1.0 - sc.b2t;
+        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int i = lo + tid + k * NT;
@@ -468,7 +466,7 @@ __global__ __launch_bounds__(NT) void team_solve_kernel(SolveArgs a) {
                         sv = sv_c[i];
                     }
                     const double g = (G.x * v.x + G.y * v.y) / vmi;
-                    vmi = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vmi, g, mv, sv);
+                    vmi = opt_update(os, vmi, g, mv, sv);
                     if (!REG) {
                         vm_c[i] = vmi;
                         mv_c[i] = mv;
@@ -481,7 +479,7 @@ __global__ __launch_bounds__(NT) void team_solve_kernel(SolveArgs a) {
                         sa = sa_c[i];
                     }
                     const double g = G.y * v.x - G.x * v.y;
-                    vai = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vai, g, ma, sa);
+                    vai = opt_update(os, vai, g, ma, sa);
                     if (!REG) {
                         va_c[i] = vai;
                         ma_c[i] = ma;
@@ -694,8 +692,7 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
         sc.t_step += 1.0;
         sc.b1t *= a.b1;
         sc.b2t *= a.b2;
-        const double bc1 = 1.0 - sc.b1t;
-        const double bc2 = 1.0 - sc.b2t;
+        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
         DPF_BUS_LOOP_BEGIN
                 const int il = (int)i - lo;
                 // every global load of this bus first, so that they overlap the gather
@@ -711,16 +708,13 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
                 if (il == of) h = csub(h, csub(cmul(oyd, Xw[of]), cmul(oy, Xw[ot])));
                 else if (il == ot) h = csub(h, csub(cmul(oyd, Xw[ot]), cmul(oy, Xw[of])));
                 const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
-                double2 v;
-                {
-                    double sn0, cs0;
-                    fast_sincos(vai, sn0, cs0);
-                    v = make_double2(vmi * cs0, vmi * sn0);
-                }
+                double sn0, cs0;
+                fast_sincos(vai, sn0, cs0);
+                const double2 v = make_double2(vmi * cs0, vmi * sn0);
                 if (tk == kPQ) {
-                    const double g = (G.x * v.x + G.y * v.y) / vmi;
+                    const double g = grad_vm(G, cs0, sn0, vmi);
                     double mv = mv0, sv = sv0;
-                    vmi = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vmi, g, mv, sv);
+                    vmi = opt_update(os, vmi, g, mv, sv);
                     vm_c[i] = vmi;
                     mv_c[i] = mv;
                     sv_c[i] = sv;
@@ -728,15 +722,16 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
                 if (tk != kSlack) {
                     const double g = G.y * v.x - G.x * v.y;
                     double ma = ma0, sa = sa0;
-                    vai = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vai, g, ma, sa);
+                    vai = opt_update(os, vai, g, ma, sa);
                     va_c[i] = vai;
                     ma_c[i] = ma;
                     sa_c[i] = sa;
                 }
-                double sn, cs;
-                fast_sincos(vai, sn, cs);
-                v = make_double2(vmi * cs, vmi * sn);
-                if (dbl) Xv[il] = v;
+                if (dbl) {
+                    double sn, cs;
+                    fast_sincos(vai, sn, cs);
+                    Xv[il] = make_double2(vmi * cs, vmi * sn);
+                }
         DPF_BUS_LOOP_END
         sched_step(a, sc, loss);
         if (!dbl) {
@@ -920,8 +915,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
         sc.t_step += 1.0;
         sc.b1t *= a.b1;
         sc.b2t *= a.b2;
-        const double bc1 = 1.0 - sc.b1t;
-        const double bc2 = 1.0 - sc.b2t;
+        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
         // one barrier-free pass (w stays in X throughout), then the new V is
         // rebuilt from |V| and theta in a refill pass
         for (int s = 0; s < nb; ++s) {
@@ -943,12 +937,9 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     h = sell_row<4, false>(sval, scol, base, wdt, il, [&](int j) { return X[j]; }, h);
                     if (il == of) h = csub(h, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
                     else if (il == ot) h = csub(h, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
-                    double2 v;
-                    {
-                        double sn0, cs0;
-                        fast_sincos(vai, sn0, cs0);
-                        v = make_double2(vmi * cs0, vmi * sn0);
-                    }
+                    double sn0, cs0;
+                    fast_sincos(vai, sn0, cs0);
+                    const double2 v = make_double2(vmi * cs0, vmi * sn0);
                     // the seed of the A/W sweep, rebuilt from I and the same V
                     const double2 d = csub(cmulc(v, I), sp);
                     const double rP = tk != kSlack ? d.x : 0.0;
@@ -956,9 +947,9 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     const double2 ai = cmul(make_double2(two_over_m * rP, two_over_m * rQ), I);
                     const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
                     if (tk == kPQ) {
-                        const double g = (G.x * v.x + G.y * v.y) / vmi;
+                        const double g = grad_vm(G, cs0, sn0, vmi);
                         double mv = mv0, sv = sv0;
-                        vmi = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vmi, g, mv, sv);
+                        vmi = opt_update(os, vmi, g, mv, sv);
                         vm_c[i] = vmi;
                         mv_c[i] = mv;
                         sv_c[i] = sv;
@@ -966,7 +957,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     if (tk != kSlack) {
                         const double g = G.y * v.x - G.x * v.y;
                         double ma = ma0, sa = sa0;
-                        vai = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vai, g, ma, sa);
+                        vai = opt_update(os, vai, g, ma, sa);
                         va_c[i] = vai;
                         ma_c[i] = ma;
                         sa_c[i] = sa;

@@ -377,8 +377,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
         sc.t_step += 1.0;
         sc.b1t *= a.b1;
         sc.b2t *= a.b2;
-        const double bc1 = 1.0 - sc.b1t;
-        const double bc2 = 1.0 - sc.b2t;
+        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
         for (int il = rlo + tid; il < rhi; il += NT) {
             const int8_t tk = btp[il];
             const double2 I = Ig[il];
@@ -392,21 +391,18 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
             h = sell_row<4, true>(sval, scol, base, wdt, il, [&](int j) { return X[j]; }, h);
             if (il == of) h = csub(h, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
             else if (il == ot) h = csub(h, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
-            double2 v;
-            {
-                double sn0, cs0;
-                fast_sincos(vai, sn0, cs0);
-                v = make_double2(vmi * cs0, vmi * sn0);
-            }
+            double sn0, cs0;
+            fast_sincos(vai, sn0, cs0);
+            const double2 v = make_double2(vmi * cs0, vmi * sn0);
             const double2 d = csub(cmulc(v, I), sp);
             const double rP = tk != kSlack ? d.x : 0.0;
             const double rQ = tk == kPQ ? d.y : 0.0;
             const double2 ai = cmul(make_double2(two_over_m * rP, two_over_m * rQ), I);
             const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
             if (tk == kPQ) {
-                const double g = (G.x * v.x + G.y * v.y) / vmi;
+                const double g = grad_vm(G, cs0, sn0, vmi);
                 double mv = mv0, sv = sv0;
-                vmi = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vmi, g, mv, sv);
+                vmi = opt_update(os, vmi, g, mv, sv);
                 st(vm_c + il, vmi);
                 mv_c[il] = mv;
                 sv_c[il] = sv;
@@ -414,7 +410,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
             if (tk != kSlack) {
                 const double g = G.y * v.x - G.x * v.y;
                 double ma = ma0, sa = sa0;
-                vai = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vai, g, ma, sa);
+                vai = opt_update(os, vai, g, ma, sa);
                 st(va_c + il, vai);
                 ma_c[il] = ma;
                 sa_c[il] = sa;

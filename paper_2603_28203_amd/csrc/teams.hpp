@@ -534,8 +534,7 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
         sc.t_step += 1.0;
         sc.b1t *= a.b1;
         sc.b2t *= a.b2;
-        const double bc1 = 1.0 - sc.b1t;
-        const double bc2 = 1.0 - sc.b2t;
+        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
         for (int k = 0; k < nchunk; ++k) {
             const int il = row_of(k);
             if (il >= rhi) continue;
@@ -551,22 +550,19 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
             if (il == of) h = csub(h, csub(cmul(oyd, xat(of, rW)), cmul(oy, xat(ot, rW))));
             else if (il == ot) h = csub(h, csub(cmul(oyd, xat(ot, rW)), cmul(oy, xat(of, rW))));
             // V of this row, rebuilt from |V| and theta (the same bits the owner published)
-            double2 v;
-            {
-                double sn0, cs0;
-                fast_sincos(vai, sn0, cs0);
-                v = make_double2(vmi * cs0, vmi * sn0);
-            }
+            double sn0, cs0;
+            fast_sincos(vai, sn0, cs0);
+            const double2 v = make_double2(vmi * cs0, vmi * sn0);
             const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
             if (tk != kSlack) {
                 const double2 p1 = P1[il], p2 = P2[il];
                 double mv = p1.x, ma = p1.y, sv = p2.x, sa = p2.y;
                 if (tk == kPQ) {
-                    const double g = (G.x * v.x + G.y * v.y) / vmi;
-                    vmi = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vmi, g, mv, sv);
+                    const double g = grad_vm(G, cs0, sn0, vmi);
+                    vmi = opt_update(os, vmi, g, mv, sv);
                 }
                 const double g = G.y * v.x - G.x * v.y;
-                vai = opt_update(a.opt, sc.lr, a.b1, a.b2, a.eps, bc1, bc2, vai, g, ma, sa);
+                vai = opt_update(os, vai, g, ma, sa);
                 P0[il] = make_double2(vmi, vai);
                 P1[il] = make_double2(mv, ma);
                 P2[il] = make_double2(sv, sa);

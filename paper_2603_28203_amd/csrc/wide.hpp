@@ -305,12 +305,12 @@ __global__ __launch_bounds__(256) void wide_phase_b_kernel(WideArgs a) {
     const double2 v = a.Vg[o];
     const int8_t tk = a.bt[r];
     const double lr = it.lr_use;
-    const double bc1 = 1.0 - it.b1t, bc2 = 1.0 - it.b2t;
+    const OptStep os = opt_step(a.opt, lr, a.b1, a.b2, a.eps, 1.0 - it.b1t, 1.0 - it.b2t);
     double vmi = a.vm[o], vai = a.va[o];
     if (tk == kPQ) {
         const double g = (G.x * v.x + G.y * v.y) / vmi;
         double mv = a.st[o], sv = a.st[2 * a.st_stride + o];
-        vmi = opt_update(a.opt, lr, a.b1, a.b2, a.eps, bc1, bc2, vmi, g, mv, sv);
+        vmi = opt_update(os, vmi, g, mv, sv);
         a.vm[o] = vmi;
         a.st[o] = mv;
         a.st[2 * a.st_stride + o] = sv;
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256) void wide_phase_b_kernel(WideArgs a) {
     if (tk != kSlack) {
         const double g = G.y * v.x - G.x * v.y;
         double ma = a.st[a.st_stride + o], sa = a.st[3 * a.st_stride + o];
-        vai = opt_update(a.opt, lr, a.b1, a.b2, a.eps, bc1, bc2, vai, g, ma, sa);
+        vai = opt_update(os, vai, g, ma, sa);
         a.va[o] = vai;
         a.st[a.st_stride + o] = ma;
         a.st[3 * a.st_stride + o] = sa;
