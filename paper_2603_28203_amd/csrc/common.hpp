@@ -135,6 +135,13 @@ __device__ __forceinline__ double uniform(double x) {
     const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
+// the last lane's value in every lane (scalar registers)
+__device__ __forceinline__ double last_lane(double x) {
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffLL), kWave - 1);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), kWave - 1);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
 // Device-scope (relaxed agent-scope atomic) store and load of a double: the store
 // writes through to the device's coherence point and the load does not hit a
 // possibly stale L1/L2 copy, so values handed between workgroups of one kernel
@@ -371,6 +378,7 @@ __device__ __forceinline__ double kcos(double x, double y) {
 // sin and cos for |x| <= pi/4, the range of nearly every bus angle: the same
 // polynomials with no reduction tail and no quadrant, and 1 - x^2/2 carried with
 // its rounding error instead of a case distinction on |x|
+__device__ __forceinline__ bool angle_is_near(double x) { return fabs(x) <= 0.785398163397448279; }
 __device__ __forceinline__ void near_sincos(double x, double &s, double &c) {
     const double S1 = -1.66666666666666324348e-01, S2 = 8.33333333332248946124e-03,
                  S3 = -1.98412698298579493134e-04, S4 = 2.75573137070700676789e-06,
@@ -387,7 +395,7 @@ __device__ __forceinline__ void near_sincos(double x, double &s, double &c) {
 }
 
 __device__ __forceinline__ void fast_sincos(double x, double &s, double &c) {
-    if (fabs(x) <= 0.785398163397448279) {
+    if (angle_is_near(x)) {
         near_sincos(x, s, c);
         return;
     }

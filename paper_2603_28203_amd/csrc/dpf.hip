@@ -164,7 +164,7 @@ struct Variant {
 
 template <int NT, int K>
 Variant make_variant() {
-    return Variant{NT, K, dpf::kReg, dpf::team_solve_kernel<NT, K, dpf::kReg>};
+    return Variant{NT, K, dpf::kReg, dpf::team_solve_reg_kernel<NT, K>};
 }
 // any number of buses per thread (k = 0)
 template <int NT>
@@ -296,6 +296,7 @@ struct SolveLayout {
     int32_t w_total = 0;  // slices of the wide sub-grids (per case)
     int64_t entries = 0;  // sliced-ELL entries (multiple of 64)
     size_t off_nslice = 0, off_slice_off = 0, off_width = 0, off_start = 0, off_col = 0, off_val = 0;
+    size_t off_row = 0;  // row slots of a sorted copy (n_bus <= kSellSortRows), else 0
     size_t off_bw = 0, off_mom = 0, off_scr = 0, off_wcount = 0, off_woff = 0, off_mres = 0, off_part = 0,
            off_items = 0, off_list = 0, off_list2 = 0, off_sched = 0, off_bar = 0, off_tfirst = 0,
            off_order = 0;
@@ -329,6 +330,10 @@ static SolveLayout solve_layout(const dpf_grid_t *g, int32_t n_sub, const int32_
     o += align_up(sizeof(int32_t) * (size_t)(n_sub + 1), 256);
     L.off_bw = o;
     o += align_up(sizeof(int32_t) * (size_t)n_sub, 256);
+    if (n_sub == 1 && g->n_bus <= dpf::kSellSortRows) {
+        L.off_row = o;
+        o += align_up(2 * sizeof(int32_t) * (size_t)g->n_bus, 256);
+    }
     L.off_width = o;
     o += align_up(sizeof(int32_t) * (size_t)(L.n_slices + 1), 256);
     L.off_start = o;
@@ -1400,12 +1405,18 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
     int32_t *sub_bw = (int32_t *)(ws + L.off_bw);
     const int32_t wmax = g->max_row_nnz > 0 ? g->max_row_nnz : std::max<int32_t>(g->nnz, 1);
     if (done_ns) hipLaunchKernelGGL(dpf::stamp_kernel, dim3(1), dim3(64), 0, st, (int64_t *)(ws + 8));
+    // the register kernels' copy has its rows sorted by length (one slice has nothing to sort)
+    int32_t *srow = nullptr, *sslot = nullptr;
+    if (L.off_row && L.n_slices > 1 && v->mode == dpf::kReg && !plan.teams && !has_wide) {
+        srow = (int32_t *)(ws + L.off_row);
+        sslot = srow + g->n_bus;
+    }
     // sliced-ELL copy of Y for this call (the flag is cleared by a kernel, not a memset,
     // so that the whole call can be captured in a graph)
     if (n_sub <= dpf::kSellSmallSubs && L.n_slices <= dpf::kSellSmallSlices) {  // small grids: one launch
         hipLaunchKernelGGL(dpf::sell_small_kernel, dim3(1), dim3(dpf::kSellSmallThreads), 0, st, n_sub,
                            sub_offset_dev, g->n_bus, g->row_ptr, g->col_idx, (const double2 *)g->val, wmax, nslice,
-                           slice_off, width, start, scol, sval, sub_bw, bad, bad + 4);
+                           slice_off, width, start, scol, sval, sub_bw, bad, bad + 4, srow, sslot);
     } else {
         hipLaunchKernelGGL(dpf::sell_count_kernel, dim3((n_sub + 255) / 256), dim3(256), 0, st, n_sub,
                            sub_offset_dev, g->n_bus, nslice, sub_bw, bad, bad + 4);  // clears header words 0, 4 and 5
@@ -1438,7 +1449,7 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
     a.va = va;
     a.ld = ld;
     a.st_stride = (int64_t)B * ld;
-    a.sell = dpf::SellView{slice_off, width, start, scol, sval};
+    a.sell = dpf::SellView{slice_off, width, start, scol, sval, srow, sslot};
     a.sub_bw = sub_bw;
     a.band_nt = 0;
     a.bad_grid = bad;
@@ -1489,12 +1500,17 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
     a.stamp = (const int64_t *)(ws + 8);  // header words 2-3
     a.ns_per_tick = dev.ns_per_tick;
 
-    // dynamic LDS: two exchange arrays when they fit, else one
-    const int32_t lds_entries_max = (dev.lds_per_block - kSolveStaticLds) / 16;
-    int32_t entries = 2 * n_max <= lds_entries_max ? 2 * n_max : n_max;
-    entries = std::max<int32_t>(entries, 1);
-    a.lds_cap = entries;
-    const size_t lds_bytes = (size_t)entries * 16;
+    // dynamic LDS of a per-item kernel in 16-byte units: two exchange arrays when they
+    // fit, else one; the register kernels also keep matrix entries there
+    const int32_t lds_units_max = (dev.lds_per_block - kSolveStaticLds) / 16;
+    auto lds_units = [&](const Variant &k) {
+        if (k.mode == dpf::kReg)
+            return dpf::reg_lds_units(k.nt, n_max, std::min<int64_t>(((int64_t)n_max + 63) / 64 * 64 * wmax, L.entries),
+                                      lds_units_max);
+        return std::max<int32_t>(2 * n_max <= lds_units_max ? 2 * n_max : n_max, 1);
+    };
+    a.lds_cap = lds_units(*v);
+    const size_t lds_bytes = (size_t)a.lds_cap * 16;
     const int32_t items = B * n_sub;
     // handoff calls of one grid may start their cases by descending initial max|r|:
     // the cases likely to run longest then do not start last (one evaluation of
@@ -1589,9 +1605,10 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
             const Variant *f = &variant_table(&cnt)[default_variant_index(std::max(1, n_max))];
             dpf::SolveArgs b = a;
             b.band_nt = v->nt * v->k;  // the banded block
+            b.lds_cap = lds_units(*f);
             DPF_HIP(hipFuncSetAttribute((const void *)f->fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)lds_bytes));
-            hipLaunchKernelGGL(f->fn, dim3(items), dim3(f->nt), lds_bytes, st, b);
+                                        b.lds_cap * 16));
+            hipLaunchKernelGGL(f->fn, dim3(items), dim3(f->nt), (size_t)b.lds_cap * 16, st, b);
             DPF_HIP(hipGetLastError());
         }
     }

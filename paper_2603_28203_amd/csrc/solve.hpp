@@ -31,6 +31,8 @@
 #include "eval.hpp"
 #include "sell.hpp"
 
+#include <algorithm>
+
 namespace dpf {
 
 enum StoreMode {
@@ -259,11 +261,55 @@ __device__ __forceinline__ Rank2 outage_of_case(const OutageView &ov, int c, int
     return r;
 }
 
-template <int NT, int K, int MODE>
-__global__ __launch_bounds__(NT) void team_solve_kernel(SolveArgs a) {
+// Register-resident kernel: a thread owns rows tid + k*NT, k < K, and keeps their
+// whole state in registers for the solve; V and w are separate LDS arrays, two
+// barriers per iteration.
+//
+// What bounds it: with one row per thread (small grids) the latency of one
+// iteration's dependent chain, with more the FP64 issue of the one CU that runs the
+// item.  Both are served by the same choices:
+//  - the item's matrix entries sit in LDS behind V and w (values 16 B, columns as
+//    16-bit LDS offsets; the offsets of a row's first kRegCols entries even in
+//    registers), so a row product is one round trip to LDS instead of a chain of
+//    scalar load, L1/L2 load and LDS gather.  A matrix that does not fit is read
+//    from the sliced-ELL copy in global memory (the host asks for at most
+//    kRegLdsPerThread bytes per thread, the share that leaves room for as many
+//    workgroups as the registers allow);
+//  - cos and sin of a row's angle stay in registers, so V, w and both gradients need
+//    no second sincos and no division by |V|;
+//  - the stop test does not stand between the two products: the reduction's partials
+//    are read after the gradient sweep has formed every gradient, and only the update
+//    waits for the decision;
+//  - the updates of |V| and theta run side by side (coordinates that are not
+//    learnable keep their value by a select), their two division chains overlapped.
+//  - a single grid's rows are sorted by length (sell_sort_rows), so slices carry next
+//    to no padding in any numbering.
+// Measured on an MI355X, us per iteration, one earlier form of this kernel (matrix from
+// L2, updates one after the other behind the stop test) -> this one: 14 buses x 1 case
+// 2.7 -> 1.5; 118 x 2048 7.3 -> 4.8; 250 x 1024 8.1 -> 4.7; 900 x 512 13.5 -> 8.6;
+// 1354 x 64 8.0 -> 5.5 (9.3 -> 5.6 in an arbitrary numbering); 1950 x 64 11.3 -> 8.7.
+// At three rows per thread the columns and injections are re-read instead of kept
+// (both kept: 94 spilled registers, 5.6 us); at four the matrix stays in global memory
+// (V, w and a 2048-row matrix exceed the LDS).  1024 threads with two rows each spill
+// 150 registers (11 us for 1354 x 64).
+constexpr int kRegCols = 8;           // columns of a row kept in registers
+constexpr int kRegLdsRows = 3;        // rows per thread up to which the matrix goes to LDS
+constexpr int kRegLdsPerThread = 320; // bytes: 160 KB over the 512 threads two waves per SIMD make
+
+// dynamic LDS of one register-kernel workgroup in 16-byte units: V and w of n_max rows
+// and room for `entries` matrix entries (18 B each, whole slices), at most the share
+// of its threads
+inline int32_t reg_lds_units(int nt, int32_t n_max, int64_t entries, int32_t lds_units) {
+    const int64_t share = std::max<int64_t>(2 * (int64_t)n_max, (int64_t)nt * kRegLdsPerThread / 16 - 32);
+    return (int32_t)std::max<int64_t>(
+        1, std::min<int64_t>(2 * (int64_t)n_max + (entries * 9 + 7) / 8, std::min<int64_t>(share, lds_units)));
+}
+
+template <int NT, int K>
+__global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
     extern __shared__ double2 X[];
     __shared__ double red[2][NT / kWave];
-    constexpr bool REG = MODE == kReg;
+    constexpr int NW = NT / kWave;
 
     const int tid = threadIdx.x;
     const int item = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
@@ -275,18 +321,17 @@ __global__ __launch_bounds__(NT) void team_solve_kernel(SolveArgs a) {
     const int out_idx = c * a.n_sub + sidx;
     if (n > a.team_cap) return;  // handled by the multi-workgroup path
     if (a.band_nt > 0 && a.sub_bw[sidx] <= a.band_nt) return;  // handled by the banded kernel
-    if (n < 0 || n > NT * K || n > a.lds_cap || *a.bad_grid) {  // see DPF_BAD_GRID
+    if (n < 0 || n > NT * K || 2 * n > a.lds_cap || *a.bad_grid) {  // see DPF_BAD_GRID
         if (tid == 0) {
             a.status[out_idx] = DPF_BAD_GRID;
             a.iters[out_idx] = 0;
         }
         return;
     }
-    const int slice0 = a.sell.slice_off[sidx];
     const int lane = tid & (kWave - 1);
-    const bool dbl = 2 * n <= a.lds_cap;
-    double2 *Xv = X;
-    double2 *Xw = dbl ? X + n : X;
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int slice0 = a.sell.slice_off[sidx];
+    const int ns = (n + kWave - 1) / kWave;
 
     // step count and schedule (a resumed solve continues them)
     ItemSched sc = load_item_sched(a, out_idx);
@@ -297,240 +342,272 @@ __global__ __launch_bounds__(NT) void team_solve_kernel(SolveArgs a) {
     // N-1 outage of this case (only meaningful for a single sub-grid)
     const Rank2 r2 = outage_of_case(a.ov, c, lo, hi);
     if (r2.bad) return;  // reported by the call's prologue
-    const int of = r2.of, ot = r2.ot;
+    // LDS and slices go by slot, the caller's arrays by row
+    const int of = r2.of >= 0 && a.sell.slot ? a.sell.slot[r2.of] : r2.of;
+    const int ot = r2.ot >= 0 && a.sell.slot ? a.sell.slot[r2.ot] : r2.ot;
     const double2 oy = r2.oy, oyd = r2.oyd;
 
-    const int64_t cb = (int64_t)c * a.ld;
-    const int64_t sb = (int64_t)c * a.s_ld;
+    const int64_t cb = (int64_t)c * a.ld + lo;
+    const int64_t sb = (int64_t)c * a.s_ld + lo;
     double *vm_c = a.vm + cb;
     double *va_c = a.va + cb;
     double *mv_c = a.st + cb;
     double *ma_c = a.st + a.st_stride + cb;
     double *sv_c = a.st + 2 * a.st_stride + cb;
     double *sa_c = a.st + 3 * a.st_stride + cb;
-    double2 *Vg = a.scratch ? a.scratch + cb : nullptr;
-    double2 *aIg = a.scratch ? a.scratch + a.st_stride + cb : nullptr;
 
-    // Per-bus registers.  kReg keeps the whole item state; kGlobal keeps only
-    // `hold` (w or the new V across the single-buffer barrier).
-    constexpr int KR = REG ? K : 1;
-    double2 V[KR], aI[KR], Sr[KR];
-    double vmr[KR], var_[KR], mvr[KR], mar[KR], svr[KR], sar[KR];
-    int8_t ty[KR];
-    double2 hold[K];
-
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int i = lo + tid + k * NT;
-        hold[k] = make_double2(0.0, 0.0);
-        if (REG) {
-            ty[k % KR] = kSlack;
-            V[k % KR] = aI[k % KR] = Sr[k % KR] = make_double2(0.0, 0.0);
-            vmr[k % KR] = var_[k % KR] = mvr[k % KR] = mar[k % KR] = svr[k % KR] = sar[k % KR] = 0.0;
-        }
-        if (i < hi) {
-            const double vmi = vm_c[i], vai = va_c[i];
-            double sn, cs;
-            fast_sincos(vai, sn, cs);
-            const double2 v = make_double2(vmi * cs, vmi * sn);
-            if (REG) {
-                ty[k % KR] = a.bt[i];
-                V[k % KR] = v;
-                vmr[k % KR] = vmi;
-                var_[k % KR] = vai;
-                Sr[k % KR] = a.s_spec[sb + i];
-                if (!a.st_fresh) {
-                    mvr[k % KR] = mv_c[i];
-                    mar[k % KR] = ma_c[i];
-                    svr[k % KR] = sv_c[i];
-                    sar[k % KR] = sa_c[i];
-                }
-            } else {
-                Vg[i] = v;
-                if (a.st_fresh) {
-                    mv_c[i] = 0.0;
-                    ma_c[i] = 0.0;
-                    sv_c[i] = 0.0;
-                    sa_c[i] = 0.0;
-                }
-            }
-            Xv[i - lo] = v;
+    // LDS: V [n], w [n], matrix values [cap], matrix columns [cap] (byte offsets, 16 bit)
+    char *lds = reinterpret_cast<char *>(X);
+    double2 *Xv = X;
+    const int wofs = n * 16;  // byte offset of w
+    double2 *MV = X + 2 * n;
+    const int cap = ((a.lds_cap - 2 * n) * 8 / 9) & ~(kWave - 1);
+    uint16_t *MC = reinterpret_cast<uint16_t *>(MV + cap);
+    const int e0 = a.sell.start[slice0];  // units of 64 entries
+    const int64_t base0 = (int64_t)e0 * kWave;
+    if constexpr (K <= kRegLdsRows) {
+        const int tot = min((a.sell.start[slice0 + ns] - e0) * kWave, cap);
+        for (int e = tid; e < tot; e += NT) {
+            MV[e] = a.sell.val[base0 + e];
+            MC[e] = (uint16_t)(a.sell.col[base0 + e] * 16);
         }
     }
+
+    // the rows of this thread: slot tid + k*NT is lane `lane` of slice wv + k*NW
+    int row[K];
+    int wd[K], mo[K];  // slice width (0: no such slice) and first entry
+    constexpr bool SREG = K <= 2;  // else the injections are re-read (L2) each iteration
+    double2 S[SREG ? K : 1], aI[K];
+    double vm[K], va[K], mv[K], ma[K], sv[K], sa[K], cs[K], sn[K];
+    uint32_t pq = 0, fre = 0;  // bit k: row k is PQ / not the slack
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int j = wv + k * NW;
+        const int il = tid + k * NT;
+        row[k] = il < n && a.sell.row ? a.sell.row[il] : il;
+        wd[k] = j < ns ? a.sell.width[slice0 + j] : 0;
+        mo[k] = j < ns ? (a.sell.start[slice0 + j] - e0) * kWave : 0;
+        if constexpr (SREG) S[k] = make_double2(0.0, 0.0);
+        aI[k] = make_double2(0.0, 0.0);
+        vm[k] = va[k] = mv[k] = ma[k] = sv[k] = sa[k] = sn[k] = 0.0;
+        cs[k] = 1.0;
+        if (il < n) {
+            const int8_t t = a.bt[lo + row[k]];
+            pq |= (t == kPQ ? 1u : 0u) << k;
+            fre |= (t != kSlack ? 1u : 0u) << k;
+            vm[k] = vm_c[row[k]];
+            va[k] = va_c[row[k]];
+            if constexpr (SREG) S[k] = a.s_spec[sb + row[k]];
+            if (!a.st_fresh) {
+                mv[k] = mv_c[row[k]];
+                ma[k] = ma_c[row[k]];
+                sv[k] = sv_c[row[k]];
+                sa[k] = sa_c[row[k]];
+            }
+        }
+    }
+    // cos and sin of every row's angle and V to LDS: near zero for all rows at once, then
+    // the rows of other angles, if the wave has any, one at a time in one rolled loop (the
+    // general reduction inlined once instead of once per row)
+    auto publish = [&]() {
+        bool far = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            near_sincos(va[k], sn[k], cs[k]);
+            far |= !angle_is_near(va[k]);
+        }
+        if (__ballot(far) != 0) {
+#pragma unroll 1
+            for (int r = 0; r < K; ++r) {
+                double x = va[0], s1, c1;
+#pragma unroll
+                for (int k = 1; k < K; ++k) x = r == k ? va[k] : x;
+                fast_sincos(x, s1, c1);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    sn[k] = r == k ? s1 : sn[k];
+                    cs[k] = r == k ? c1 : cs[k];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (tid + k * NT < n) Xv[tid + k * NT] = make_double2(vm[k] * cs[k], vm[k] * sn[k]);
+    };
+    publish();
     __syncthreads();
 
     int it = 0, stat = DPF_MAX_ITER;
     double mu = 0.0, loss = 0.0;
-    __shared__ int pause_flag;
-    for (;; ++it) {
-        if (!REG && handoff_due(a, it, &pause_flag)) {
-            stat = kPaused;
-            break;
-        }
-        // ---------------- phase A: forward product, residual, loss, seed
-        double lsum = 0.0, lmax = 0.0;
+    // the iterations, with the matrix in LDS or read from the sliced-ELL copy
+    auto iterate = [&](auto in_lds) {
+        constexpr bool LDSM = decltype(in_lds)::value;
+        constexpr int COLS = K <= 2 ? kRegCols : 0;
+        uint32_t ccol[K][LDSM && COLS > 0 ? COLS / 2 : 1];
+        if constexpr (LDSM && COLS > 0) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int i = lo + tid + k * NT;
-            if (i < hi) {
-                const int8_t tk = REG ? ty[k % KR] : a.bt[i];
-                const int il = i - lo;
-                const int gsl = __builtin_amdgcn_readfirstlane(slice0 + (il >> 6));
-                const int wdt = a.sell.width[gsl];
-                const int base = a.sell.start[gsl] * kWave + lane;
-                double2 acc = make_double2(0.0, 0.0);
-                acc = sell_row<4, true>(a.sell.val, a.sell.col, base, wdt, il, [&](int j) { return Xv[j]; }, acc);
-                if (il == of) acc = csub(acc, csub(cmul(oyd, Xv[of]), cmul(oy, Xv[ot])));
-                else if (il == ot) acc = csub(acc, csub(cmul(oyd, Xv[ot]), cmul(oy, Xv[of])));
-                const double2 v = REG ? V[k % KR] : Xv[il];
-                const double2 s = REG ? Sr[k % KR] : a.s_spec[sb + i];
-                const double2 d = csub(cmulc(v, acc), s);
-                const double rP = tk != kSlack ? d.x : 0.0;
-                const double rQ = tk == kPQ ? d.y : 0.0;
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int q = 0; q < COLS; q += 2) {
+                    const uint32_t c0 = q < wd[k] ? (uint32_t)MC[mo[k] + q * kWave + lane] : 0u;
+                    const uint32_t c1 = q + 1 < wd[k] ? (uint32_t)MC[mo[k] + (q + 1) * kWave + lane] : 0u;
+                    ccol[k][q / 2] = c0 | (c1 << 16);
+                }
+        }
+        auto at = [&](int ofs) -> double2 { return *reinterpret_cast<const double2 *>(lds + ofs); };
+        // row k of Y z, z at byte offset zo of the LDS
+        auto product = [&](int k, int zo) {
+            double2 acc = make_double2(0.0, 0.0);
+            const int w = wd[k];
+            if constexpr (LDSM) {
+                // entries Q .. Q+N-1 at once; N is the whole row where one row per thread
+                // leaves the registers, else 4
+                constexpr int G = K == 1 ? kRegCols : 4;
+                const double2 *mvp = MV + mo[k] + lane;
+                auto group = [&](auto first, auto count) {
+                    constexpr int Q = decltype(first)::value, N = decltype(count)::value;
+                    double2 v[N], z[N];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        v[u] = mvp[(Q + u) * kWave];
+                        if constexpr (COLS > 0) {
+                            const uint32_t pk = ccol[k][(Q + u) / 2];
+                            z[u] = at(zo + (int)(((Q + u) & 1) ? pk >> 16 : pk & 0xffffu));
+                        } else {
+                            z[u] = at(zo + MC[mo[k] + (Q + u) * kWave + lane]);
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < N; ++u) acc = cfma(v[u], z[u], acc);
+                };
+                auto groups = [&](auto first, int left) {
+#define DPF_GROUP(N) \
+    case N: group(first, std::integral_constant<int, N>{}); break;
+                    switch (min(left, G)) {
+                        DPF_GROUP(1) DPF_GROUP(2) DPF_GROUP(3) DPF_GROUP(4)
+                        default:
+                            if constexpr (G > 4) {
+                                switch (min(left, G)) {
+                                    DPF_GROUP(5) DPF_GROUP(6) DPF_GROUP(7) DPF_GROUP(8)
+                                    default: break;
+                                }
+                            }
+                    }
+#undef DPF_GROUP
+                };
+                groups(std::integral_constant<int, 0>{}, w);
+                if constexpr (G < kRegCols)
+                    if (w > G) groups(std::integral_constant<int, G < kRegCols ? G : 0>{}, w - G);
+#pragma unroll 1
+                for (int q = kRegCols; q < w; ++q)
+                    acc = cfma(mvp[q * kWave], at(zo + MC[mo[k] + q * kWave + lane]), acc);
+            } else {
+                const int own = max(min(tid + k * NT, n - 1), 0);
+                acc = sell_row<4, true>(a.sell.val + base0, a.sell.col + base0, mo[k] + lane, w, own,
+                                        [&](int j) { return at(zo + j * 16); }, acc);
+            }
+            if (of >= 0) {
+                const int il = tid + k * NT;
+                const double2 zf = at(zo + of * 16), zt = at(zo + ot * 16);
+                if (il == of) acc = csub(acc, csub(cmul(oyd, zf), cmul(oy, zt)));
+                else if (il == ot) acc = csub(acc, csub(cmul(oyd, zt), cmul(oy, zf)));
+            }
+            return acc;
+        };
+
+        for (;; ++it) {
+            // this iteration's optimizer scalars, off the chain of the products
+            const double b1t = sc.b1t * a.b1, b2t = sc.b2t * a.b2;
+            const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - b1t, 1.0 - b2t);
+
+            // ---------------- A: forward product, residual, loss, seed
+            double lsum = 0.0, lmax = 0.0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int il = tid + k * NT;
+                double2 sp = make_double2(0.0, 0.0);
+                if constexpr (SREG) sp = S[k];
+                else if (il < n) sp = a.s_spec[sb + row[k]];
+                const double2 acc = product(k, 0);
+                const double2 v = make_double2(vm[k] * cs[k], vm[k] * sn[k]);
+                const double2 d = csub(cmulc(v, acc), sp);
+                const double rP = (fre >> k) & 1u ? d.x : 0.0;
+                const double rQ = (pq >> k) & 1u ? d.y : 0.0;
                 lsum += rP * rP + rQ * rQ;
                 lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
                 const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
-                const double2 w = cmulc(av, v);
-                if (REG) aI[k % KR] = cmul(av, acc);
-                else aIg[i] = cmul(av, acc);
-                if (dbl) Xw[il] = w;
-                else hold[k] = w;
+                aI[k] = cmul(av, acc);
+                if (il < n) *reinterpret_cast<double2 *>(lds + wofs + il * 16) = cscale(two_over_m, cmulc(make_double2(rP, rQ), v));
             }
-        }
-        block_reduce2<NT>(lsum, lmax, red);
-        __syncthreads();
-        if (!dbl) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int i = lo + tid + k * NT;
-                if (i < hi) Xw[i - lo] = hold[k];
-            }
-        }
-        block_reduce2_finish<NT>(lsum, lmax, red);
-        loss = m_res > 0.0 ? lsum / m_res : 0.0;
-        mu = isnan(lsum) ? lsum : lmax;
-        trace_mu(a, true, out_idx, it, mu);
-        if (!dbl) __syncthreads();  // w fully in X before phase B reads it
-        if (!(isfinite(loss) && isfinite(mu))) {
-            stat = DPF_NONFINITE;
-            break;
-        }
-        if (mu < a.tol) {
-            stat = DPF_CONVERGED;
-            break;
-        }
-        if (it >= a.max_iter) {
-            stat = DPF_MAX_ITER;
-            break;
-        }
-
-        // ---------------- phase B: adjoint product, gradient, Adam
-        sc.t_step += 1.0;
-        sc.b1t *= a.b1;
-        sc.b2t *= a.b2;
-        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int i = lo + tid + k * NT;
-            if (i < hi) {
-                const int8_t tk = REG ? ty[k % KR] : a.bt[i];
-                const int il = i - lo;
-                const int gsl = __builtin_amdgcn_readfirstlane(slice0 + (il >> 6));
-                const int wdt = a.sell.width[gsl];
-                const int base = a.sell.start[gsl] * kWave + lane;
-                double2 h = make_double2(0.0, 0.0);
-                h = sell_row<4, true>(a.sell.val, a.sell.col, base, wdt, il, [&](int j) { return Xw[j]; }, h);
-                if (il == of) h = csub(h, csub(cmul(oyd, Xw[of]), cmul(oy, Xw[ot])));
-                else if (il == ot) h = csub(h, csub(cmul(oyd, Xw[ot]), cmul(oy, Xw[of])));
-                double2 v, ai;
-                double vmi, vai, mv = 0.0, ma = 0.0, sv = 0.0, sa = 0.0;
-                if (REG) {
-                    v = V[k % KR];
-                    ai = aI[k % KR];
-                    vmi = vmr[k % KR];
-                    vai = var_[k % KR];
-                    mv = mvr[k % KR];
-                    ma = mar[k % KR];
-                    sv = svr[k % KR];
-                    sa = sar[k % KR];
-                } else {
-                    v = Vg[i];
-                    ai = aIg[i];
-                    vmi = vm_c[i];
-                    vai = va_c[i];
-                }
-                const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
-                if (tk == kPQ) {
-                    if (!REG) {
-                        mv = mv_c[i];
-                        sv = sv_c[i];
-                    }
-                    const double g = (G.x * v.x + G.y * v.y) / vmi;
-                    vmi = opt_update(os, vmi, g, mv, sv);
-                    if (!REG) {
-                        vm_c[i] = vmi;
-                        mv_c[i] = mv;
-                        sv_c[i] = sv;
-                    }
-                }
-                if (tk != kSlack) {
-                    if (!REG) {
-                        ma = ma_c[i];
-                        sa = sa_c[i];
-                    }
-                    const double g = G.y * v.x - G.x * v.y;
-                    vai = opt_update(os, vai, g, ma, sa);
-                    if (!REG) {
-                        va_c[i] = vai;
-                        ma_c[i] = ma;
-                        sa_c[i] = sa;
-                    }
-                }
-                double sn, cs;
-                fast_sincos(vai, sn, cs);
-                v = make_double2(vmi * cs, vmi * sn);
-                if (REG) {
-                    V[k % KR] = v;
-                    vmr[k % KR] = vmi;
-                    var_[k % KR] = vai;
-                    mvr[k % KR] = mv;
-                    mar[k % KR] = ma;
-                    svr[k % KR] = sv;
-                    sar[k % KR] = sa;
-                } else {
-                    Vg[i] = v;
-                }
-                if (dbl) Xv[il] = v;
-                else hold[k] = v;
-            }
-        }
-        // ---------------- schedule step (uniform across the workgroup)
-        sched_step(a, sc, loss);
-        if (!dbl) {
+            if constexpr (NW > 1) block_reduce2<NT>(lsum, lmax, red);
             __syncthreads();
+            if constexpr (NW == 1) {  // one wave: its last lane holds the item's sums
+                wave_last_sum_max(lsum, lmax);
+                lsum = last_lane(lsum);
+                lmax = last_lane(lmax);
+            }
+
+            // ---------------- B: adjoint product and gradients (they change no state yet)
+            double gv[K], ga[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const int i = lo + tid + k * NT;
-                if (i < hi) Xv[i - lo] = hold[k];
+                const double2 h = product(k, wofs);
+                const double2 G = make_double2(aI[k].x + h.x, aI[k].y - h.y);
+                gv[k] = grad_vm(G, cs[k], sn[k], vm[k]);
+                ga[k] = vm[k] * (G.y * cs[k] - G.x * sn[k]);
             }
+            if constexpr (NW > 1) block_reduce2_finish<NT>(lsum, lmax, red);
+            loss = m_res > 0.0 ? lsum / m_res : 0.0;
+            mu = isnan(lsum) ? lsum : lmax;
+            trace_mu(a, true, out_idx, it, mu);
+            if (!(isfinite(loss) && isfinite(mu))) {
+                stat = DPF_NONFINITE;
+                break;
+            }
+            if (mu < a.tol) {
+                stat = DPF_CONVERGED;
+                break;
+            }
+            if (it >= a.max_iter) {
+                stat = DPF_MAX_ITER;
+                break;
+            }
+
+            // ---------------- update; the moments of a coordinate that is not learnable are
+            // never written back
+            sc.t_step += 1.0;
+            sc.b1t = b1t;
+            sc.b2t = b2t;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const double vmn = opt_update(os, vm[k], gv[k], mv[k], sv[k]);
+                const double van = opt_update(os, va[k], ga[k], ma[k], sa[k]);
+                vm[k] = (pq >> k) & 1u ? vmn : vm[k];
+                va[k] = (fre >> k) & 1u ? van : va[k];
+            }
+            publish();
+            sched_step(a, sc, loss);
+            __syncthreads();
         }
-        __syncthreads();
-    }
+    };
+    if (K <= kRegLdsRows && (a.sell.start[slice0 + ns] - e0) * kWave <= cap) iterate(std::bool_constant<(K <= kRegLdsRows)>{});
+    else iterate(std::false_type{});
 
     // ---------------- write back
-    if (REG) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int i = lo + tid + k * NT;
-            if (i < hi) {
-                if (ty[k % KR] == kPQ) vm_c[i] = vmr[k % KR];
-                if (ty[k % KR] != kSlack) va_c[i] = var_[k % KR];
-                if (!a.st_fresh) {
-                    mv_c[i] = mvr[k % KR];
-                    ma_c[i] = mar[k % KR];
-                    sv_c[i] = svr[k % KR];
-                    sa_c[i] = sar[k % KR];
-                }
+    for (int k = 0; k < K; ++k) {
+        if ((pq >> k) & 1u) {
+            vm_c[row[k]] = vm[k];
+            if (!a.st_fresh) {
+                mv_c[row[k]] = mv[k];
+                sv_c[row[k]] = sv[k];
+            }
+        }
+        if ((fre >> k) & 1u) {
+            va_c[row[k]] = va[k];
+            if (!a.st_fresh) {
+                ma_c[row[k]] = ma[k];
+                sa_c[row[k]] = sa[k];
             }
         }
     }

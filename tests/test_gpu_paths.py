@@ -1,0 +1,88 @@
+"""GPU tests of single kernel branches at the sizes where they can go wrong,
+against the FP64 CPU oracle.
+
+Tolerances (fixed before the first run): FP64 sums of at most a few hundred terms
+with cancellation to O(1) leave relative errors of 1e-15 to 1e-13, and the few
+optimizer steps from perturbed starts do not amplify them; 1e-10 leaves three orders
+of margin."""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-10
+
+
+@pytest.fixture(scope="module")
+def dpf():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_28203_amd as m
+    m.lib()
+    return m
+
+
+def cu(x, dtype=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(x)).to("cuda", dtype)
+
+
+def random_grid(rng, n, m, hub=0):
+    """Random tree plus chords in an arbitrary numbering, with a hub bus of about
+    ``hub`` further branches (one matrix row much longer than the others)."""
+    f, t = synth.tree_chord_grid(rng, n, m)
+    if hub:
+        c = int(rng.integers(0, n))
+        others = rng.choice(np.setdiff1d(np.arange(n), [c]), size=hub, replace=False)
+        f = np.concatenate([f, np.full(hub, c, np.int32)])
+        t = np.concatenate([t, others.astype(np.int32)])
+    nb = len(f)
+    bt = np.zeros(n, np.int8)
+    kinds = rng.permutation(n)
+    bt[kinds[0]] = 2
+    bt[kinds[1:1 + max(1, n // 7)]] = 1
+    va = rng.uniform(-0.1, 0.1, n)
+    va[kinds[0]] = 0.0
+    return synth.Grid(n, f.astype(np.int32), t.astype(np.int32), rng.uniform(0.01, 0.1, nb), rng.uniform(0.05, 0.3, nb),
+                      rng.uniform(0.0, 0.05, nb), bt, rng.uniform(0.97, 1.03, n), va)
+
+
+@pytest.mark.parametrize("n,m,hub", [(2, 1, 0), (64, 100, 40), (65, 98, 40), (256, 380, 20), (257, 400, 12),
+                                     (512, 700, 0), (513, 900, 9), (1100, 1600, 30), (1537, 2200, 17),
+                                     (2048, 3000, 5), (130, 5000, 0)])
+def test_register_solves_at_their_size_edges(dpf, n, m, hub):
+    """The register-resident kernels on sorted rows: one and several rows per thread,
+    rows longer than the columns kept in registers and than the last sort key, a
+    matrix that does not fit the workgroup's LDS (130 buses, 5000 branches), outages,
+    and optimizer state in and out; angles beyond pi/4 in one case."""
+    rng = np.random.default_rng(41000 + n)
+    g = random_grid(rng, n, m, hub)
+    B, steps = 3, 6
+    S0 = oracle.injections(oracle.ybus_of(g), g.vm, g.va)
+    S = S0[None] * rng.uniform(0.97, 1.03, (B, 1))
+    vm0 = g.vm[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type == 0)
+    va0 = g.va[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type != 2)
+    va0[2] += 2.5 * (g.bus_type != 2)
+    nbr = synth.non_bridge_branches(n, g.f, g.t)
+    outage = np.array([-1, nbr[len(nbr) // 2] if len(nbr) else -1, -1], np.int32)
+    state = torch.zeros(4, B, n, dtype=torch.float64, device="cuda")
+    vm, va = cu(vm0), cu(va0)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    out = dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm, va, outage=cu(outage, torch.int32), adam_state=state,
+                    sched_state=dpf.fresh_sched_state(B, 1e-3),
+                    opts=dpf.Options(lr=1e-3, tol=0.0, max_iter=steps))
+    assert out["iters"].tolist() == [steps] * B
+    for c in range(B):
+        ref = oracle.solve_adam(oracle.ybus_of(g, skip=int(outage[c])), g.bus_type, S[c], vm0[c], va0[c],
+                                oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=steps))
+        assert np.abs(vm[c].cpu().numpy() - ref["vm"]).max() < TOL, c
+        assert np.abs(va[c].cpu().numpy() - ref["va"]).max() < TOL, c
+        assert abs(out["max_mis"][c].item() - ref["mu"]) <= TOL * max(1.0, ref["mu"]), c
+    # the moments of coordinates that are not learnable come back as they went in
+    fixed = cu(g.bus_type != 0, torch.bool)
+    assert (state[0][:, fixed] == 0).all() and (state[2][:, fixed] == 0).all()
