@@ -234,6 +234,11 @@ __device__ __forceinline__ OptStep opt_step(int kind, double lr, double b1, doub
 
 // One update of a learnable coordinate x with gradient g and state m (first
 // moment / momentum buffer), s (second moment).
+__device__ __forceinline__ double adam_update(const OptStep &o, double x, double g, double &m, double &s) {
+    m = o.b1 * m + (1.0 - o.b1) * g;
+    s = o.b2 * s + (1.0 - o.b2) * (g * g);
+    return x - o.rate * (m / (sqrt(s * o.q2) + o.eps));
+}
 __device__ __forceinline__ double opt_update(const OptStep &o, double x, double g, double &m, double &s) {
     if (o.kind == 1) {
         m = o.b1 * m + g;
@@ -243,9 +248,20 @@ __device__ __forceinline__ double opt_update(const OptStep &o, double x, double 
         s = o.b2 * s + (1.0 - o.b2) * (g * g);
         return x - o.rate * (g / (sqrt(s) + o.eps));
     }
-    m = o.b1 * m + (1.0 - o.b1) * g;
-    s = o.b2 * s + (1.0 - o.b2) * (g * g);
-    return x - o.rate * (m / (sqrt(s * o.q2) + o.eps));
+    return adam_update(o, x, g, m, s);
+}
+// both coordinates of a bus; Adam's two division chains in one basic block, so that
+// they overlap
+__device__ __forceinline__ void opt_update2(const OptStep &o, double &x, double gx, double &mx, double &sx, double &y,
+                                            double gy, double &my, double &sy) {
+    if (o.kind == 0) {
+        const double xn = adam_update(o, x, gx, mx, sx), yn = adam_update(o, y, gy, my, sy);
+        x = xn;
+        y = yn;
+    } else {
+        x = opt_update(o, x, gx, mx, sx);
+        y = opt_update(o, y, gy, my, sy);
+    }
 }
 
 // d loss / d|V| = Re(conj(G) V) / |V| with V = vm (cs + j sn): the division cancels,

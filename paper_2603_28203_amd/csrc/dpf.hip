@@ -160,11 +160,17 @@ struct Variant {
     int k;
     int mode;
     KernelFn fn;
+    bool resident = false;  // kReg above 2048 buses: a*I in the scratch when the LDS is short
 };
 
 template <int NT, int K>
 Variant make_variant() {
     return Variant{NT, K, dpf::kReg, dpf::team_solve_reg_kernel<NT, K>};
+}
+// the same for sub-grids above the register kernels' 2048 buses
+template <int NT, int K>
+Variant make_resident_variant() {
+    return Variant{NT, K, dpf::kReg, dpf::team_solve_resident_kernel<NT, K>, true};
 }
 // any number of buses per thread (k = 0)
 template <int NT>
@@ -183,10 +189,10 @@ Variant make_pair_variant() {
 }
 
 
-// Register-resident variants up to 2048 buses per item, the 1024-thread streaming
-// variant above (any size).  The banded variants (k = buses per thread per block)
+// Register-resident variants up to 4096 buses per item (the last two entries above
+// 2048), the 1024-thread streaming variant above (any size).  The banded variants (k = buses per thread per block)
 // serve sub-grids whose bandwidth is at most threads * k; the others go to the
-// default variant of the size in the same call.  The last entry is not a
+// default variant of the size in the same call.  The kWide entry is not a
 // workgroup-per-item kernel: it sends every sub-grid of the call to the
 // multi-workgroup path, which spreads one item over many CUs.  Kinds measured and
 // retired as dominated on every workload timed (64 to 4096 cases of 300 to 9241
@@ -200,6 +206,7 @@ const Variant *variant_table(int *count) {
         make_variant<512, 4>(),         make_stream_variant<1024>(),  make_band_variant<1024, 2>(),
         make_band_variant<1024, 4>(),   make_pair_variant<1024, 4>(), make_pair_variant<1024, 2>(),
         Variant{0, 0, dpf::kWide, nullptr},
+        make_resident_variant<512, 6>(), make_resident_variant<512, 8>(),
     };
     *count = (int)(sizeof(table) / sizeof(table[0]));
     return table;
@@ -225,34 +232,43 @@ int items_bucket(int64_t items) { return items <= 64 ? 0 : (items <= 256 ? 1 : 2
 // streaming kernel, 29 against 39 us).
 constexpr int32_t kWideDefaultBuses = 2048;
 
-// first workgroup-per-item (non-banded) variant that holds n_max buses
-int default_variant_index(int32_t n_max) {
+// first register-resident variant that holds n_max buses, else the streaming one.
+// small_only: no register-resident variant above 2048 buses, for calls that may hand
+// their items over (those kernels cannot) and calls of several sub-grids (their threads
+// carry 6 or 8 rows also for an item of a few)
+int default_variant_index(int32_t n_max, bool small_only = false) {
     int cnt = 0;
     const Variant *t = variant_table(&cnt);
     for (int i = 0; i < cnt; ++i)
-        if (!dpf::is_banded(t[i].mode) && t[i].mode != dpf::kWide && variant_fits(t[i], n_max)) return i;
+        if (t[i].mode == dpf::kReg && !(small_only && t[i].resident) && variant_fits(t[i], n_max)) return i;
+    for (int i = 0; i < cnt; ++i)
+        if (t[i].mode == dpf::kGlobal && variant_fits(t[i], n_max)) return i;
     return -1;
 }
 
 int wide_variant_index() {
     int cnt = 0;
-    variant_table(&cnt);
-    return cnt - 1;
+    const Variant *t = variant_table(&cnt);
+    int i = 0;
+    while (t[i].mode != dpf::kWide) ++i;
+    return i;
 }
 
 // forced >= 0: the call's route names the variant (nullptr if it cannot hold n_max).
 // *few_large: the multi-workgroup path was chosen by default for few large items
 // (not from the autotune cache or the route)
-const Variant *pick_variant(int32_t n_max, int64_t items, int n_cu, int forced = -1, bool *few_large = nullptr) {
+const Variant *pick_variant(int32_t n_max, int64_t items, int n_cu, int forced = -1, bool *few_large = nullptr,
+                            bool small_only = false) {
     int cnt = 0;
     const Variant *t = variant_table(&cnt);
-    int d = default_variant_index(n_max);
+    const int d = default_variant_index(n_max, small_only);
+    const int size_class = default_variant_index(n_max);
     if (few_large) *few_large = false;
     if (d < 0) return nullptr;
     if (forced >= 0) return forced < cnt && variant_fits(t[forced], n_max) ? &t[forced] : nullptr;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        const int c = g_tune_init ? g_tune[d][items_bucket(items)] : -1;
+        const int c = g_tune_init ? g_tune[size_class][items_bucket(items)] : -1;
         if (c >= 0 && c < cnt && variant_fits(t[c], n_max)) return &t[c];
     }
     if (n_max > kWideDefaultBuses && items <= n_cu / 2) {
@@ -307,7 +323,7 @@ struct SolveLayout {
 
 static SolveLayout solve_layout(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offset, int32_t B,
                                 int32_t ld, bool streaming, int32_t team_cap, bool handoff = false,
-                                bool pairs = false, bool teams = false) {
+                                bool pairs = false, bool teams = false, bool resident = false) {
     SolveLayout L;
     int64_t team_part = 0;  // member partials: at most min(slices, members cap) per item
     for (int32_t s = 0; s < (sub_offset ? n_sub : 1); ++s) {
@@ -348,6 +364,10 @@ static SolveLayout solve_layout(const dpf_grid_t *g, int32_t n_sub, const int32_
         L.off_scr = o;  // V, a*I and w [3][B][ld] complex (paired state: I and the three pairs, [4][B][ld];
                         // persistent teams: a*I, V, w and the three pairs, [6][B][ld])
         o += align_up(sizeof(double2) * (teams ? 6 : pairs ? 4 : 3) * (size_t)B * ld, 256);
+    }
+    if (resident && !streaming) {
+        L.off_scr = o;  // a*I [B][ld] complex
+        o += align_up(sizeof(double2) * (size_t)B * ld, 256);
     }
     if (wide) {
         L.off_wcount = o;
@@ -1291,7 +1311,7 @@ static CallPlan plan_call(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub
     p.has_small = small > 0;
     bool few_large = false;
     p.v = pick_variant(std::max(1, p.n_max), (int64_t)B * small, dev.n_cu > 0 ? dev.n_cu : 256, route.variant,
-                       &few_large);
+                       &few_large, route.tail_handoff > 0 || (sub_offset && n_sub > 1));
     if (forced_bad) *forced_bad = route.variant >= 0 && !p.v;
     // few large items of one grid that the split kernel can hold, with the split
     // kernel enabled: it runs them from the first iteration (the multi-workgroup
@@ -1338,7 +1358,8 @@ size_t dpf_solve_workspace_bytes(const dpf_grid_t *g, int32_t n_sub, const int32
     const CallPlan p = plan_call(g, n_sub, sub_offset, B, dev, rt, &forced_bad);
     if (forced_bad) return 0;
     return solve_layout(g, n_sub, sub_offset, B, ld, p.v && p.v->mode != dpf::kReg, p.cap,
-                        p.handoff > 0 || p.split_direct, p.v && p.v->mode == dpf::kPair && p.has_small, p.teams)
+                        p.handoff > 0 || p.split_direct, p.v && p.v->mode == dpf::kPair && p.has_small, p.teams,
+                        p.v && p.v->resident)
         .total;
 }
 
@@ -1390,7 +1411,7 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
         return fail(DPF_EUNSUPPORTED, "route.tail_device: the grid is too large for the split kernel");
     const bool pairs = v->mode == dpf::kPair && has_small;
     const SolveLayout L = solve_layout(g, n_sub, sub_offset, B, ld, v->mode != dpf::kReg, cap,
-                                       handoff || plan.split_direct, pairs, plan.teams);
+                                       handoff || plan.split_direct, pairs, plan.teams, v->resident);
     const bool has_wide = L.w_total > 0;
     if (!workspace || ws_bytes < L.total) return fail(DPF_ENOMEM, "workspace too small");
     hipStream_t st = (hipStream_t)stream;
@@ -1462,7 +1483,7 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
         a.scratch = (double2 *)(ws + L.off_scr);
         a.st = adam_state ? adam_state : mom;
     } else {
-        a.scratch = nullptr;
+        a.scratch = v->resident ? (double2 *)(ws + L.off_scr) : nullptr;
         a.st = adam_state;  // may be null: fresh moments kept in registers only
     }
     a.st_fresh = adam_state ? 0 : 1;
@@ -1504,6 +1525,7 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
     // fit, else one; the register kernels also keep matrix entries there
     const int32_t lds_units_max = (dev.lds_per_block - kSolveStaticLds) / 16;
     auto lds_units = [&](const Variant &k) {
+        if (k.resident) return 3 * n_max <= lds_units_max ? 3 * n_max : 2 * n_max;
         if (k.mode == dpf::kReg)
             return dpf::reg_lds_units(k.nt, n_max, std::min<int64_t>(((int64_t)n_max + 63) / 64 * 64 * wmax, L.entries),
                                       lds_units_max);
@@ -1602,7 +1624,7 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
         if (dpf::is_banded(v->mode)) {
             // items whose bandwidth exceeds the banded block go to the general variant
             int cnt = 0;
-            const Variant *f = &variant_table(&cnt)[default_variant_index(std::max(1, n_max))];
+            const Variant *f = &variant_table(&cnt)[default_variant_index(std::max(1, n_max), handoff || n_sub > 1)];
             dpf::SolveArgs b = a;
             b.band_nt = v->nt * v->k;  // the banded block
             b.lds_cap = lds_units(*f);

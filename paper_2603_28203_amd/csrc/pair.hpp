@@ -132,7 +132,7 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
     double mu = 0.0, loss = 0.0;
     __shared__ int pause_flag;
     for (;; ++it) {
-        if (handoff_due(a, it, &pause_flag)) {
+        if (handoff_due(it, &pause_flag)) {
             stat = kPaused;
             break;
         }
@@ -185,26 +185,16 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
         block_reduce2_finish<NT>(lsum, lmax, red);
         loss = m_res > 0.0 ? lsum / m_res : 0.0;
         mu = isnan(lsum) ? lsum : lmax;
-        trace_mu(a, true, out_idx, it, mu);
-        if (!(isfinite(loss) && isfinite(mu))) {
-            stat = DPF_NONFINITE;
-            break;
-        }
-        if (mu < a.tol) {
-            stat = DPF_CONVERGED;
-            break;
-        }
-        if (it >= a.max_iter) {
-            stat = DPF_MAX_ITER;
+        trace_mu(cold_args(), true, out_idx, it, mu);
+        const int stop = stop_status(cold_args(), loss, mu, it);
+        if (stop >= 0) {
+            stat = stop;
             break;
         }
 
         // ---------------- gradient sweep: one barrier-free pass (w stays in X), then
         // the new V refilled from the updated pairs
-        sc.t_step += 1.0;
-        sc.b1t *= a.b1;
-        sc.b2t *= a.b2;
-        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
+        const OptStep os = begin_update(cold_args(), sc);
         for (int s = 0; s < nb; ++s) {
 #pragma unroll
             for (int j = 0; j < J; ++j) {
@@ -250,11 +240,11 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
         }
         __syncthreads();
         refill();
-        sched_step(a, sc, loss);
+        sched_step(cold_args(), sc, loss);
         __syncthreads();
     }
 
-    if (tid == 0) finish_item(a, out_idx, it, stat, mu, loss, sc);
+    if (tid == 0) finish_item(out_idx, it, stat, mu, loss, sc);
 }
 
 }  // namespace dpf

@@ -150,7 +150,7 @@ constexpr int kSellSmallSlices = 64;
 // meshed grid in an arbitrary numbering the longest of 64 rows is twice the mean, so
 // half of an unsorted copy is padding (and a 1354-bus grid's copy then misses the LDS:
 // 8.0 against 5.4 us per iteration of 64 such cases).
-constexpr int kSellSortRows = 2048;
+constexpr int kSellSortRows = 4096;
 constexpr int kSellSortKeys = 16;
 
 __device__ __forceinline__ void sell_sort_rows(int32_t n, const int32_t *__restrict__ rp, int32_t *row, int32_t *slot,

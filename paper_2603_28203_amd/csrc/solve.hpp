@@ -97,6 +97,20 @@ struct SolveArgs {
     double ns_per_tick;
 };
 
+// The kernel's SolveArgs (the first argument of every solve kernel) read from the
+// kernel-argument segment where they are needed.  What an iteration uses once
+// (optimizer, schedule, trace, stop test) is read this way: as ordinary arguments
+// the compiler keeps all of them in scalar registers across the loops, spills 100 to
+// 200 of those to vector lanes, and the FP64 constants end up in vector registers.
+// (The one-row register kernels, whose iteration is one latency chain, take them as
+// ordinary arguments: 1.43 against 1.52 us per iteration of a 14-bus solve.)
+typedef const __attribute__((address_space(4))) SolveArgs ColdArgs;
+__device__ __forceinline__ ColdArgs *cold_args() {
+    ColdArgs *p = (ColdArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 template <int NT>
 __device__ __forceinline__ void block_reduce2(double &s, double &m, double (*red)[NT / kWave]) {
     wave_last_sum_max(s, m);
@@ -149,9 +163,10 @@ __device__ __forceinline__ ItemSched load_item_sched(const SolveArgs &a, int out
 // item's persistent step count, so a call resumed from its schedule state keeps
 // the phase of the decay (PyTorch's StepLR counts scheduler steps across epochs
 // the same way).
-__device__ __forceinline__ void sched_step(const SolveArgs &a, ItemSched &s, double loss) {
-    if (a.sch == DPF_SCHED_PLATEAU) {
-        if (loss < s.best * (1.0 - a.threshold)) {
+template <typename A>
+__device__ __forceinline__ void sched_step(A *p, ItemSched &s, double loss) {
+    if (p->sch == DPF_SCHED_PLATEAU) {
+        if (loss < s.best * (1.0 - p->threshold)) {
             s.best = loss;
             s.bad = 0;
         } else {
@@ -161,16 +176,33 @@ __device__ __forceinline__ void sched_step(const SolveArgs &a, ItemSched &s, dou
             s.cool -= 1;
             s.bad = 0;
         }
-        if (s.bad > a.patience) {
-            double nl = s.lr * a.factor;
-            if (nl < a.min_lr) nl = a.min_lr;
-            if (s.lr - nl > a.sched_eps) s.lr = nl;
-            s.cool = a.cooldown;
+        if (s.bad > p->patience) {
+            double nl = s.lr * p->factor;
+            if (nl < p->min_lr) nl = p->min_lr;
+            if (s.lr - nl > p->sched_eps) s.lr = nl;
+            s.cool = p->cooldown;
             s.bad = 0;
         }
-    } else if (a.sch == DPF_SCHED_STEP) {
-        if (a.patience > 0 && ((int64_t)s.t_step % a.patience) == 0) s.lr = s.lr * a.factor;
+    } else if (p->sch == DPF_SCHED_STEP) {
+        if (p->patience > 0 && ((int64_t)s.t_step % p->patience) == 0) s.lr = s.lr * p->factor;
     }
+}
+
+// the stop test of Algorithm 1, before an update: the item's status, or -1 to go on
+template <typename A>
+__device__ __forceinline__ int stop_status(A *p, double loss, double mu, int it) {
+    if (!(isfinite(loss) && isfinite(mu))) return DPF_NONFINITE;
+    if (mu < p->tol) return DPF_CONVERGED;
+    return it >= p->max_iter ? DPF_MAX_ITER : -1;
+}
+
+// one more update: the step count and beta powers, and the update's scalars
+template <typename A>
+__device__ __forceinline__ OptStep begin_update(A *p, ItemSched &s) {
+    s.t_step += 1.0;
+    s.b1t *= p->b1;
+    s.b2t *= p->b2;
+    return opt_step(p->opt, s.lr, p->b1, p->b2, p->eps, 1.0 - s.b1t, 1.0 - s.b2t);
 }
 
 // Tail handoff.  Early retirement leaves the last items of a batch alone on
@@ -179,11 +211,12 @@ __device__ __forceinline__ void sched_step(const SolveArgs &a, ItemSched &s, dou
 // memory, schedule in a.sched) and the host finishes them on the multi-workgroup
 // path, which spreads every item over many CUs.  Checked every 32 iterations;
 // thread 0 reads the counter and the decision reaches the workgroup through LDS.
-__device__ __forceinline__ bool handoff_due(const SolveArgs &a, int it, int *flag) {
-    if (a.handoff <= 0 || it == 0 || (it & 31) != 0) return false;
+__device__ __forceinline__ bool handoff_due(int it, int *flag) {
+    ColdArgs *p = cold_args();
+    if (p->handoff <= 0 || it == 0 || (it & 31) != 0) return false;
     if (threadIdx.x == 0)
-        *flag = a.total_items - __hip_atomic_load(a.done_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <=
-                a.handoff;
+        *flag = p->total_items - __hip_atomic_load(p->done_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <=
+                p->handoff;
     __syncthreads();
     return *flag != 0;
 }
@@ -191,22 +224,24 @@ __device__ __forceinline__ bool handoff_due(const SolveArgs &a, int it, int *fla
 // optional trace of the stop-test quantity: max|r| of iteration `it` of this call
 // (tested before its update) goes to slot it / trace_every when it is a multiple
 // of trace_every and the slot exists; one thread writes (thread 0 of `writer`)
-__device__ __forceinline__ void trace_mu(const SolveArgs &a, bool writer, int out_idx, int it, double mu) {
-    if (a.trace_len > 0 && writer && threadIdx.x == 0 && it % a.trace_every == 0 && it / a.trace_every < a.trace_len)
-        a.trace[(int64_t)out_idx * a.trace_len + it / a.trace_every] = mu;
+template <typename A>
+__device__ __forceinline__ void trace_mu(A *p, bool writer, int out_idx, int it, double mu) {
+    if (p->trace_len > 0 && writer && threadIdx.x == 0 && it % p->trace_every == 0 && it / p->trace_every < p->trace_len)
+        p->trace[(int64_t)out_idx * p->trace_len + it / p->trace_every] = mu;
 }
 
 // per-item results and the schedule state, written by one thread
-__device__ __forceinline__ void finish_item(const SolveArgs &a, int out_idx, int it, int stat, double mu, double loss,
+__device__ __forceinline__ void finish_item(int out_idx, int it, int stat, double mu, double loss,
                                             const ItemSched &s) {
-    if (a.handoff > 0 && stat != kPaused) atomicAdd(a.done_count, 1);
-    a.iters[out_idx] = it;
-    a.status[out_idx] = stat;
-    a.mu_out[out_idx] = mu;
-    a.loss_out[out_idx] = loss;
-    if (a.done_ns) a.done_ns[out_idx] = (int64_t)((double)(wall_clock64() - *a.stamp) * a.ns_per_tick);
-    if (a.sched) {
-        double *ss = a.sched + kSchedWords * (int64_t)out_idx;
+    ColdArgs *p = cold_args();
+    if (p->handoff > 0 && stat != kPaused) atomicAdd(p->done_count, 1);
+    p->iters[out_idx] = it;
+    p->status[out_idx] = stat;
+    p->mu_out[out_idx] = mu;
+    p->loss_out[out_idx] = loss;
+    if (p->done_ns) p->done_ns[out_idx] = (int64_t)((double)(wall_clock64() - *p->stamp) * p->ns_per_tick);
+    if (p->sched) {
+        double *ss = p->sched + kSchedWords * (int64_t)out_idx;
         ss[0] = s.t_step;
         ss[1] = s.lr;
         ss[2] = s.best;
@@ -261,6 +296,13 @@ __device__ __forceinline__ Rank2 outage_of_case(const OutageView &ov, int c, int
     return r;
 }
 
+// an index whose address arithmetic is re-derived where it is used instead of being
+// hoisted out of the iterations and kept live
+__device__ __forceinline__ uint32_t opaque_index(uint32_t i) {
+    asm volatile("" : "+v"(i));
+    return i;
+}
+
 // Register-resident kernel: a thread owns rows tid + k*NT, k < K, and keeps their
 // whole state in registers for the solve; V and w are separate LDS arrays, two
 // barriers per iteration.
@@ -310,6 +352,10 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
     extern __shared__ double2 X[];
     __shared__ double red[2][NT / kWave];
     constexpr int NW = NT / kWave;
+    auto args = [&]() {
+        if constexpr (K == 1) return &a;
+        else return cold_args();
+    };
 
     const int tid = threadIdx.x;
     const int item = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
@@ -517,8 +563,8 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
 
         for (;; ++it) {
             // this iteration's optimizer scalars, off the chain of the products
-            const double b1t = sc.b1t * a.b1, b2t = sc.b2t * a.b2;
-            const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - b1t, 1.0 - b2t);
+            ItemSched nx = sc;
+            const OptStep os = begin_update(args(), nx);
 
             // ---------------- A: forward product, residual, loss, seed
             double lsum = 0.0, lmax = 0.0;
@@ -527,7 +573,7 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
                 const int il = tid + k * NT;
                 double2 sp = make_double2(0.0, 0.0);
                 if constexpr (SREG) sp = S[k];
-                else if (il < n) sp = a.s_spec[sb + row[k]];
+                else if (il < n) sp = a.s_spec[sb + opaque_index(row[k])];
                 const double2 acc = product(k, 0);
                 const double2 v = make_double2(vm[k] * cs[k], vm[k] * sn[k]);
                 const double2 d = csub(cmulc(v, acc), sp);
@@ -559,34 +605,25 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
             if constexpr (NW > 1) block_reduce2_finish<NT>(lsum, lmax, red);
             loss = m_res > 0.0 ? lsum / m_res : 0.0;
             mu = isnan(lsum) ? lsum : lmax;
-            trace_mu(a, true, out_idx, it, mu);
-            if (!(isfinite(loss) && isfinite(mu))) {
-                stat = DPF_NONFINITE;
-                break;
-            }
-            if (mu < a.tol) {
-                stat = DPF_CONVERGED;
-                break;
-            }
-            if (it >= a.max_iter) {
-                stat = DPF_MAX_ITER;
+            trace_mu(args(), true, out_idx, it, mu);
+            const int stop = stop_status(args(), loss, mu, it);
+            if (stop >= 0) {
+                stat = stop;
                 break;
             }
 
             // ---------------- update; the moments of a coordinate that is not learnable are
             // never written back
-            sc.t_step += 1.0;
-            sc.b1t = b1t;
-            sc.b2t = b2t;
+            sc = nx;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const double vmn = opt_update(os, vm[k], gv[k], mv[k], sv[k]);
-                const double van = opt_update(os, va[k], ga[k], ma[k], sa[k]);
+                double vmn = vm[k], van = va[k];
+                opt_update2(os, vmn, gv[k], mv[k], sv[k], van, ga[k], ma[k], sa[k]);
                 vm[k] = (pq >> k) & 1u ? vmn : vm[k];
                 va[k] = (fre >> k) & 1u ? van : va[k];
             }
             publish();
-            sched_step(a, sc, loss);
+            sched_step(args(), sc, loss);
             __syncthreads();
         }
     };
@@ -611,7 +648,224 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
             }
         }
     }
-    if (tid == 0) finish_item(a, out_idx, it, stat, mu, loss, sc);
+    if (tid == 0) finish_item(out_idx, it, stat, mu, loss, sc);
+}
+
+// Resident kernel for sub-grids of 2049 to 4096 buses: the state of every row (|V|,
+// theta and the four moments) and a*I stay in registers as in the register kernel, V
+// and w are separate LDS arrays, and everything else is read where it is needed: the
+// matrix (rows sorted by length) and the injections from L2, a row's own V from LDS.
+// The streaming kernel moves 176 B of state per bus and iteration through L2 and the
+// Infinity Cache (5.4 TB/s at 256 cases of 3000 buses, its bound); this one moves none
+// and is bound by the latency of its row products (two waves per SIMD, about half of
+// the FP64 issue used).  us per iteration, streaming -> this, 256 cases: 2500 buses
+// 20 -> 14.2, 3000 24.0 -> 14.6, 4000 30.7 -> 22.7 (8 rows per thread; a*I in global
+// memory).  512 threads: 1024 spill 30 to 120 registers (15.0 us at best); gathers of
+// a group of four issued together (one at a time 17.1 us; groups of 6 or 8 16.1, 17.5).
+template <int NT, int K>
+__global__ __launch_bounds__(NT) void team_solve_resident_kernel(SolveArgs a) {
+    extern __shared__ double2 X[];
+    __shared__ double red[2][NT / kWave];
+    constexpr int NW = NT / kWave;
+
+    const int tid = threadIdx.x;
+    const int item = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
+    const int sidx = item / a.B;
+    const int c = item - sidx * a.B;
+    const int lo = a.sub_off ? a.sub_off[sidx] : 0;
+    const int hi = a.sub_off ? a.sub_off[sidx + 1] : a.n_bus;
+    const int n = hi - lo;
+    const int out_idx = c * a.n_sub + sidx;
+    if (n > a.team_cap) return;  // handled by the multi-workgroup path
+    if (a.band_nt > 0 && a.sub_bw[sidx] <= a.band_nt) return;  // handled by the banded kernel
+    if (n < 0 || n > NT * K || 2 * n > a.lds_cap || *a.bad_grid) {  // see DPF_BAD_GRID
+        if (tid == 0) {
+            a.status[out_idx] = DPF_BAD_GRID;
+            a.iters[out_idx] = 0;
+        }
+        return;
+    }
+    const int lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int slice0 = a.sell.slice_off[sidx];
+    const int ns = (n + kWave - 1) / kWave;
+    ItemSched sc = load_item_sched(a, out_idx);
+    const double m_res = residual_count<NT>(a.bt, lo, hi, red);
+    const double two_over_m = m_res > 0.0 ? 2.0 / m_res : 0.0;
+    const Rank2 r2 = outage_of_case(a.ov, c, lo, hi);
+    if (r2.bad) return;  // reported by the call's prologue
+    // LDS and slices go by slot, the caller's arrays by row
+    const int of = r2.of >= 0 && a.sell.slot ? a.sell.slot[r2.of] : r2.of;
+    const int ot = r2.ot >= 0 && a.sell.slot ? a.sell.slot[r2.ot] : r2.ot;
+    const double2 oy = r2.oy, oyd = r2.oyd;
+
+    const int64_t cb = (int64_t)c * a.ld + lo;
+    double *__restrict__ vm_c = a.vm + cb;
+    double *__restrict__ va_c = a.va + cb;
+    double *__restrict__ st_c = a.st + cb;
+    const int64_t stride = a.st_stride;
+    const double2 *__restrict__ Sc = a.s_spec + (int64_t)c * a.s_ld + lo;
+    const double2 *__restrict__ sval = a.sell.val;
+    const int32_t *__restrict__ scol = a.sell.col;
+    double2 *Xv = X, *Xw = X + n;
+    // a*I between the sweeps: a third LDS array where it fits, else the scratch
+    const bool aI_lds = 3 * n <= a.lds_cap;
+    double2 *Xa = X + 2 * n;
+    double2 *__restrict__ aIg = a.scratch + cb;
+
+    double vm[K], va[K], mv[K], ma[K], sv[K], sa[K];
+    uint32_t pq = 0, fre = 0;  // bit k: row k is PQ / not the slack
+    int row[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int il = tid + k * NT;
+        row[k] = il < n && a.sell.row ? a.sell.row[il] : il;
+        vm[k] = va[k] = mv[k] = ma[k] = sv[k] = sa[k] = 0.0;
+        if (il < n) {
+            const int r = row[k];
+            const int8_t t = a.bt[lo + r];
+            pq |= (t == kPQ ? 1u : 0u) << k;
+            fre |= (t != kSlack ? 1u : 0u) << k;
+            vm[k] = vm_c[r];
+            va[k] = va_c[r];
+            if (!a.st_fresh) {
+                mv[k] = st_c[r];
+                ma[k] = st_c[stride + r];
+                sv[k] = st_c[2 * stride + r];
+                sa[k] = st_c[3 * stride + r];
+            }
+        }
+    }
+    // V of row k to LDS, right for angles near zero; the rows of other angles, if the wave
+    // has any, follow one at a time in one rolled loop (see the register kernel)
+    bool far = false;
+    auto publish = [&](int k, int il) {
+        double sn, cs;
+        near_sincos(va[k], sn, cs);
+        far |= !angle_is_near(va[k]);
+        if (il < n) Xv[il] = make_double2(vm[k] * cs, vm[k] * sn);
+    };
+    auto publish_far = [&]() {
+        if (__ballot(far) != 0) {
+#pragma unroll 1
+            for (int r = 0; r < K; ++r) {
+                double x = va[0], m = vm[0], sn, cs;
+#pragma unroll
+                for (int k = 1; k < K; ++k) {
+                    x = r == k ? va[k] : x;
+                    m = r == k ? vm[k] : m;
+                }
+                fast_sincos(x, sn, cs);
+                if (tid + r * NT < n) Xv[tid + r * NT] = make_double2(m * cs, m * sn);
+            }
+        }
+        far = false;
+    };
+#pragma unroll
+    for (int k = 0; k < K; ++k) publish(k, tid + k * NT);
+    publish_far();
+    __syncthreads();
+
+    // row of slot il (slice j = wv + k*NW of the sub-grid, 0 entries past the last one)
+    auto product = [&](int k, int il, const double2 *Z) {
+        const int j = wv + k * NW;
+        double2 acc = make_double2(0.0, 0.0);
+        if (j < ns)
+            acc = sell_row<4, true>(sval, scol, a.sell.start[slice0 + j] * kWave + lane, a.sell.width[slice0 + j],
+                                    min(il, n - 1), [&](int q) { return Z[q]; }, acc);
+        if (of >= 0) {
+            if (il == of) acc = csub(acc, csub(cmul(oyd, Z[of]), cmul(oy, Z[ot])));
+            else if (il == ot) acc = csub(acc, csub(cmul(oyd, Z[ot]), cmul(oy, Z[of])));
+        }
+        return acc;
+    };
+
+    int it = 0, stat = DPF_MAX_ITER;
+    double mu = 0.0, loss = 0.0;
+    for (;; ++it) {
+        // ---------------- A
+        double lsum = 0.0, lmax = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int il = (int)opaque_index(tid + k * NT);
+            double2 sp = make_double2(0.0, 0.0), v = make_double2(0.0, 0.0);
+            if (il < n) {
+                sp = Sc[opaque_index(row[k])];
+                v = Xv[il];
+            }
+            const double2 acc = product(k, il, Xv);
+            const double2 d = csub(cmulc(v, acc), sp);
+            const double rP = (fre >> k) & 1u ? d.x : 0.0;
+            const double rQ = (pq >> k) & 1u ? d.y : 0.0;
+            lsum += rP * rP + rQ * rQ;
+            lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
+            const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
+            const double2 ai = cmul(av, acc);
+            if (il < n) {
+                Xw[il] = cmulc(av, v);
+                if (aI_lds) Xa[il] = ai;
+                else aIg[il] = ai;
+            }
+        }
+        block_reduce2<NT>(lsum, lmax, red);
+        __syncthreads();
+        block_reduce2_finish<NT>(lsum, lmax, red);
+        loss = m_res > 0.0 ? lsum / m_res : 0.0;
+        mu = isnan(lsum) ? lsum : lmax;
+        trace_mu(cold_args(), true, out_idx, it, mu);
+        const int stop = stop_status(cold_args(), loss, mu, it);
+        if (stop >= 0) {
+            stat = stop;
+            break;
+        }
+
+        // ---------------- B
+        const OptStep os = begin_update(cold_args(), sc);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int il = (int)opaque_index(tid + k * NT);
+            double2 ai = make_double2(0.0, 0.0), v = make_double2(0.0, 0.0);
+            if (il < n) {
+                v = Xv[il];
+                if (aI_lds) ai = Xa[il];
+                else ai = aIg[il];
+            }
+            const double2 h = product(k, il, Xw);
+            const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
+            const double gv = (G.x * v.x + G.y * v.y) / vm[k];
+            const double ga = G.y * v.x - G.x * v.y;
+            const double vmn = opt_update(os, vm[k], gv, mv[k], sv[k]);
+            asm volatile("" ::: "memory");  // one update after the other: 26 spilled registers fewer
+            const double van = opt_update(os, va[k], ga, ma[k], sa[k]);
+            vm[k] = (pq >> k) & 1u ? vmn : vm[k];
+            va[k] = (fre >> k) & 1u ? van : va[k];
+            publish(k, il);
+        }
+        publish_far();
+        sched_step(cold_args(), sc, loss);
+        __syncthreads();
+    }
+
+    // ---------------- write back (the moments of learnable coordinates only)
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int r = row[k];
+        if ((pq >> k) & 1u) {
+            vm_c[r] = vm[k];
+            if (!a.st_fresh) {
+                st_c[r] = mv[k];
+                st_c[2 * stride + r] = sv[k];
+            }
+        }
+        if ((fre >> k) & 1u) {
+            va_c[r] = va[k];
+            if (!a.st_fresh) {
+                st_c[stride + r] = ma[k];
+                st_c[3 * stride + r] = sa[k];
+            }
+        }
+    }
+    if (tid == 0) finish_item(out_idx, it, stat, mu, loss, sc);
 }
 
 // Streaming variant for large sub-grids.  Every per-bus value lives in global
@@ -622,11 +876,6 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
 // keeps the register count low enough for 1024-thread workgroups; the per-bus
 // address arithmetic is re-derived inside the iteration (opaque_index) instead
 // of being kept live.
-__device__ __forceinline__ uint32_t opaque_index(uint32_t i) {
-    asm volatile("" : "+v"(i));
-    return i;
-}
-
 template <int NT>
 __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
     extern __shared__ double2 X[];
@@ -713,7 +962,7 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
     double mu = 0.0, loss = 0.0;
     __shared__ int pause_flag;
     for (;; ++it) {
-        if (handoff_due(a, it, &pause_flag)) {
+        if (handoff_due(it, &pause_flag)) {
             stat = kPaused;
             break;
         }
@@ -750,26 +999,16 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
         block_reduce2_finish<NT>(lsum, lmax, red);
         loss = m_res > 0.0 ? lsum / m_res : 0.0;
         mu = isnan(lsum) ? lsum : lmax;
-        trace_mu(a, true, out_idx, it, mu);
+        trace_mu(cold_args(), true, out_idx, it, mu);
         if (!dbl) __syncthreads();
-        if (!(isfinite(loss) && isfinite(mu))) {
-            stat = DPF_NONFINITE;
-            break;
-        }
-        if (mu < a.tol) {
-            stat = DPF_CONVERGED;
-            break;
-        }
-        if (it >= a.max_iter) {
-            stat = DPF_MAX_ITER;
+        const int stop = stop_status(cold_args(), loss, mu, it);
+        if (stop >= 0) {
+            stat = stop;
             break;
         }
 
         // ---------------- phase B
-        sc.t_step += 1.0;
-        sc.b1t *= a.b1;
-        sc.b2t *= a.b2;
-        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
+        const OptStep os = begin_update(cold_args(), sc);
         DPF_BUS_LOOP_BEGIN
                 const int il = (int)i - lo;
                 // every global load of this bus first, so that they overlap the gather
@@ -810,7 +1049,7 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
                     Xv[il] = make_double2(vmi * cs, vmi * sn);
                 }
         DPF_BUS_LOOP_END
-        sched_step(a, sc, loss);
+        sched_step(cold_args(), sc, loss);
         if (!dbl) {
             __syncthreads();
             for (int i = lo + tid; i < hi; i += NT) {
@@ -825,7 +1064,7 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
 #undef DPF_BUS_LOOP_BEGIN
 #undef DPF_BUS_LOOP_END
 
-    if (tid == 0) finish_item(a, out_idx, it, stat, mu, loss, sc);
+    if (tid == 0) finish_item(out_idx, it, stat, mu, loss, sc);
 }
 
 // Banded variant, for sub-grids numbered with a small bandwidth: every entry of
@@ -921,7 +1160,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
     double mu = 0.0, loss = 0.0;
     __shared__ int pause_flag;
     for (;; ++it) {
-        if (handoff_due(a, it, &pause_flag)) {
+        if (handoff_due(it, &pause_flag)) {
             stat = kPaused;
             break;
         }
@@ -974,25 +1213,15 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
         block_reduce2_finish<NT>(lsum, lmax, red);
         loss = m_res > 0.0 ? lsum / m_res : 0.0;
         mu = isnan(lsum) ? lsum : lmax;
-        trace_mu(a, true, out_idx, it, mu);
-        if (!(isfinite(loss) && isfinite(mu))) {
-            stat = DPF_NONFINITE;
-            break;
-        }
-        if (mu < a.tol) {
-            stat = DPF_CONVERGED;
-            break;
-        }
-        if (it >= a.max_iter) {
-            stat = DPF_MAX_ITER;
+        trace_mu(cold_args(), true, out_idx, it, mu);
+        const int stop = stop_status(cold_args(), loss, mu, it);
+        if (stop >= 0) {
+            stat = stop;
             break;
         }
 
         // ---------------- B/U sweep
-        sc.t_step += 1.0;
-        sc.b1t *= a.b1;
-        sc.b2t *= a.b2;
-        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
+        const OptStep os = begin_update(cold_args(), sc);
         // one barrier-free pass (w stays in X throughout), then the new V is
         // rebuilt from |V| and theta in a refill pass
         for (int s = 0; s < nb; ++s) {
@@ -1049,11 +1278,11 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
             fast_sincos(va_c[i], sn, cs);
             X[i - lo] = make_double2(vmi * cs, vmi * sn);
         }
-        sched_step(a, sc, loss);
+        sched_step(cold_args(), sc, loss);
         __syncthreads();
     }
 
-    if (tid == 0) finish_item(a, out_idx, it, stat, mu, loss, sc);
+    if (tid == 0) finish_item(out_idx, it, stat, mu, loss, sc);
 }
 
 // start point of every step of a time-series window: rows [0, gridDim.y) of dst

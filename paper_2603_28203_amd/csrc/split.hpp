@@ -356,17 +356,10 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
         }
         loss = m_res > 0.0 ? lsum / m_res : 0.0;
         mu = isnan(lsum) ? lsum : lmax;
-        trace_mu(a, mem == 0, c, it, mu);
-        if (!(isfinite(loss) && isfinite(mu))) {
-            stat = DPF_NONFINITE;
-            break;
-        }
-        if (mu < a.tol) {
-            stat = DPF_CONVERGED;
-            break;
-        }
-        if (it >= a.max_iter) {
-            stat = DPF_MAX_ITER;
+        trace_mu(cold_args(), mem == 0, c, it, mu);
+        const int stop = stop_status(cold_args(), loss, mu, it);
+        if (stop >= 0) {
+            stat = stop;
             break;
         }
         // time slice used up: paused at the start of iteration it, once this launch has
@@ -374,10 +367,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
         if (slice_flag && it > it0) break;
 
         // ---------------- B: rows of this member
-        sc.t_step += 1.0;
-        sc.b1t *= a.b1;
-        sc.b2t *= a.b2;
-        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
+        const OptStep os = begin_update(cold_args(), sc);
         for (int il = rlo + tid; il < rhi; il += NT) {
             const int8_t tk = btp[il];
             const double2 I = Ig[il];
@@ -416,7 +406,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
                 sa_c[il] = sa;
             }
         }
-        sched_step(a, sc, loss);
+        sched_step(cold_args(), sc, loss);
         if (!solo) ok = team_barrier(cnt, ++nbar * T, p.limit, &bar_flag);
         else __syncthreads();
         if (!ok) {
@@ -431,7 +421,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
         *p.aborted = 1;
         stat = kPaused;
     }
-    finish_item(a, c, it, stat, mu, loss, sc);
+    finish_item(c, it, stat, mu, loss, sc);
 }
 
 // a call that starts on the split kernel: every case paused at iteration 0 and

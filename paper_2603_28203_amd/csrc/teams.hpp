@@ -516,25 +516,15 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
         }
         loss = m_res > 0.0 ? lsum / m_res : 0.0;
         mu = isnan(lsum) ? lsum : lmax;
-        trace_mu(a, mem == 0, out_idx, it, mu);
-        if (!(isfinite(loss) && isfinite(mu))) {
-            stat = DPF_NONFINITE;
-            break;
-        }
-        if (mu < a.tol) {
-            stat = DPF_CONVERGED;
-            break;
-        }
-        if (it >= a.max_iter) {
-            stat = DPF_MAX_ITER;
+        trace_mu(cold_args(), mem == 0, out_idx, it, mu);
+        const int stop = stop_status(cold_args(), loss, mu, it);
+        if (stop >= 0) {
+            stat = stop;
             break;
         }
 
         // ---------------- B: rows of this member
-        sc.t_step += 1.0;
-        sc.b1t *= a.b1;
-        sc.b2t *= a.b2;
-        const OptStep os = opt_step(a.opt, sc.lr, a.b1, a.b2, a.eps, 1.0 - sc.b1t, 1.0 - sc.b2t);
+        const OptStep os = begin_update(cold_args(), sc);
         for (int k = 0; k < nchunk; ++k) {
             const int il = row_of(k);
             if (il >= rhi) continue;
@@ -571,7 +561,7 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
                 st2(rV, il, make_double2(vmi * cs, vmi * sn));
             }
         }
-        sched_step(a, sc, loss);
+        sched_step(cold_args(), sc, loss);
         ++it;
         if (mem == 0 && tid == 0 && (it & 63) == 0) atomicAdd(progress, 1);
         if (!solo) {
@@ -583,7 +573,7 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
     }
     if (mem != 0 || tid != 0) return;
     atomicAdd(progress, 1);
-    finish_item(a, out_idx, it, ok ? stat : DPF_UNFINISHED, mu, loss, sc);
+    finish_item(out_idx, it, ok ? stat : DPF_UNFINISHED, mu, loss, sc);
 }
 
 template <int NT>

@@ -86,3 +86,36 @@ def test_register_solves_at_their_size_edges(dpf, n, m, hub):
     # the moments of coordinates that are not learnable come back as they went in
     fixed = cu(g.bus_type != 0, torch.bool)
     assert (state[0][:, fixed] == 0).all() and (state[2][:, fixed] == 0).all()
+
+
+@pytest.mark.parametrize("n,m,hub", [(2049, 3000, 30), (3072, 4300, 0), (3073, 4400, 0), (3413, 4800, 8), (4096, 5600, 0)])
+def test_resident_solves_above_the_register_kernels(dpf, n, m, hub):
+    """The default kernels of 2049 to 4096 buses with more items than fill half of the
+    device (sizes at the edges of rows per thread and of the third LDS array), with an
+    outage, optimizer state and angles beyond pi/4."""
+    rng = np.random.default_rng(42000 + n)
+    g = random_grid(rng, n, m, hub)
+    B, steps, checked = 160, 4, (0, 1, 2, 159)
+    S = oracle.injections(oracle.ybus_of(g), g.vm, g.va) * 0.98
+    vm0 = g.vm[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type == 0)
+    va0 = g.va[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type != 2)
+    va0[2] += 2.5 * (g.bus_type != 2)
+    nbr = synth.non_bridge_branches(n, g.f, g.t)
+    outage = np.full(B, -1, np.int32)
+    outage[1] = nbr[len(nbr) // 2]
+    outage[159] = nbr[0]
+    state = torch.zeros(4, B, n, dtype=torch.float64, device="cuda")
+    vm, va = cu(vm0), cu(va0)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    v = dpf.variants()[dpf.variant_for(n, B)]
+    assert v["kind"] == "register" and v["threads"] * v["buses_per_thread"] >= n
+    out = dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm, va, outage=cu(outage, torch.int32), adam_state=state,
+                    sched_state=dpf.fresh_sched_state(B, 1e-3), opts=dpf.Options(lr=1e-3, tol=0.0, max_iter=steps))
+    assert out["iters"].tolist() == [steps] * B
+    for c in checked:
+        ref = oracle.solve_adam(oracle.ybus_of(g, skip=int(outage[c])), g.bus_type, S, vm0[c], va0[c],
+                                oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=steps))
+        assert np.abs(vm[c].cpu().numpy() - ref["vm"]).max() < TOL, c
+        assert np.abs(va[c].cpu().numpy() - ref["va"]).max() < TOL, c
+    fixed = cu(g.bus_type != 0, torch.bool)
+    assert (state[0][:, fixed] == 0).all() and (state[2][:, fixed] == 0).all()
