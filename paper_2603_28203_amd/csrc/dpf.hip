@@ -883,6 +883,47 @@ int build_ybus_on(char *tmp, const YbusTemps &T, int32_t n_bus, int32_t n_branch
     return rc;
 }
 
+// One workgroup per case (eval_case_kernel) where the grid's exchange vector fits the
+// LDS (both: V and w side by side) and the cases fill enough of the device: small grids
+// always, large ones from kEvalCaseMin cases on.  Measured (us of device time, by case
+// against one thread per bus and case in three launches): 2000 x 1 15.9 against 16
+// (fewer launches, so by case), 3000 x 16 22 / 15.5, 9241 x 16 57 / 31, 3000 x 64
+// 23 / 26, 9241 x 64 65 / 80, 9241 x 256 79 / 220.
+constexpr int32_t kEvalCaseBuses = 2048;
+constexpr int32_t kEvalCaseMin = 64;
+
+using EvalFn = void (*)(dpf::EvalArgs);
+
+bool eval_by_case(int32_t n, int32_t B, bool both) {
+    const size_t lds = (size_t)n * 16 * (both ? 2 : 1);
+    return lds + 1024 <= (size_t)kGfx950LdsBytes && n <= 1024 * 10 && (n <= kEvalCaseBuses || B >= kEvalCaseMin);
+}
+
+int run_eval_by_case(const dpf::EvalArgs &a, int32_t B, bool both, hipStream_t st) {
+    struct Shape {
+        int nt, k;
+        EvalFn one, two;
+    };
+    // two: V and w side by side (at most 5 rows per thread fit the LDS)
+    static const Shape shapes[] = {
+        {64, 1, dpf::eval_case_kernel<64, 1, false>, dpf::eval_case_kernel<64, 1, true>},
+        {256, 1, dpf::eval_case_kernel<256, 1, false>, dpf::eval_case_kernel<256, 1, true>},
+        {1024, 1, dpf::eval_case_kernel<1024, 1, false>, dpf::eval_case_kernel<1024, 1, true>},
+        {1024, 2, dpf::eval_case_kernel<1024, 2, false>, dpf::eval_case_kernel<1024, 2, true>},
+        {1024, 5, dpf::eval_case_kernel<1024, 5, false>, dpf::eval_case_kernel<1024, 5, true>},
+        {1024, 10, dpf::eval_case_kernel<1024, 10, false>, nullptr},
+    };
+    const Shape *s = shapes;
+    while (a.n > s->nt * s->k) ++s;
+    const EvalFn fn = both ? s->two : s->one;
+    if (!fn) return fail(DPF_EHIP, "no evaluation kernel of this size");
+    const size_t lds = (size_t)a.n * 16 * (both ? 2 : 1);
+    DPF_HIP(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(fn, dim3(B), dim3(s->nt), lds, st, a);
+    DPF_HIP(hipGetLastError());
+    return DPF_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -964,17 +1005,23 @@ int dpf_mismatch_grad(const dpf_grid_t *g, int32_t B, int32_t ld, const int8_t *
     double2 *part = (double2 *)(ws + 256 + 3 * per);
     const int32_t nblk = (n + dpf::kEvalBlock - 1) / dpf::kEvalBlock;
     dpf::OutageView ov{outage, g->from, g->to, g->r, g->x, g->b, g->n_branch};
-    hipLaunchKernelGGL(dpf::residual_count_kernel, dim3(1), dim3(1024), 0, st, n, bus_type, m_res);
-    hipLaunchKernelGGL(dpf::polar_kernel, dim3(nblk, B), dim3(dpf::kEvalBlock), 0, st, n, (int64_t)ld, vm, va, Vw);
+    if (eval_by_case(n, B, false)) {
+        const dpf::EvalArgs e{n, g->row_ptr, g->col_idx, (const double2 *)g->val, bus_type, (const double2 *)s_spec,
+                              s_ld, ov, vm, va, ld, (double2 *)dS, loss, max_mis, g_vm, g_va, nullptr, nullptr, nullptr,
+                              nullptr, 0};
+        return run_eval_by_case(e, B, false, st);
+    }
+    hipLaunchKernelGGL(dpf::polar_kernel, dim3(nblk + 1, B), dim3(dpf::kEvalBlock), 0, st, n, (int64_t)ld, vm, va,
+                       bus_type, Vw, m_res);
     hipLaunchKernelGGL(dpf::forward_kernel, dim3(nblk, B), dim3(dpf::kEvalBlock), 0, st, n, g->row_ptr, g->col_idx,
                        (const double2 *)g->val, bus_type, (const double2 *)s_spec, (int64_t)s_ld, ov, Vw, m_res,
                        (int64_t)ld, (double2 *)dS, ww, aI, part, nullptr);
     if (g_vm)
-        hipLaunchKernelGGL(dpf::adjoint_kernel, dim3(nblk, B), dim3(dpf::kEvalBlock), 0, st, n, g->row_ptr,
+        hipLaunchKernelGGL(dpf::adjoint_kernel, dim3(nblk + 1, B), dim3(dpf::kEvalBlock), 0, st, n, g->row_ptr,
                            g->col_idx, (const double2 *)g->val, bus_type, ov, Vw, vm, (int64_t)ld, ww, aI, g_vm,
-                           g_va);
-    hipLaunchKernelGGL(dpf::finalize_kernel, dim3((B + 255) / 256), dim3(256), 0, st, B, nblk, part, m_res, loss,
-                       max_mis);
+                           g_va, part, m_res, loss, max_mis);
+    else
+        hipLaunchKernelGGL(dpf::finalize_kernel, dim3(B), dim3(dpf::kWave), 0, st, nblk, part, m_res, loss, max_mis);
     DPF_HIP(hipGetLastError());
     return DPF_OK;
 }
@@ -1010,8 +1057,14 @@ int dpf_param_grad(const dpf_grid_t *g, int32_t B, int32_t ld, const int8_t *bus
     double2 *part = (double2 *)(ws + 256 + 3 * per);
     const int32_t nblk = (n + dpf::kEvalBlock - 1) / dpf::kEvalBlock;
     dpf::OutageView ov{outage, g->from, g->to, g->r, g->x, g->b, g->n_branch};
-    hipLaunchKernelGGL(dpf::residual_count_kernel, dim3(1), dim3(1024), 0, st, n, bus_type, m_res);
-    hipLaunchKernelGGL(dpf::polar_kernel, dim3(nblk, B), dim3(dpf::kEvalBlock), 0, st, n, (int64_t)ld, vm, va, Vw);
+    if (eval_by_case(n, B, br)) {
+        const dpf::EvalArgs e{n, g->row_ptr, g->col_idx, (const double2 *)g->val, bus_type, (const double2 *)s_spec,
+                              s_ld, ov, vm, va, ld, nullptr, loss, max_mis, nullptr, nullptr, (double2 *)g_s, g_r, g_x,
+                              g_b, bld};
+        return run_eval_by_case(e, B, br, st);
+    }
+    hipLaunchKernelGGL(dpf::polar_kernel, dim3(nblk + 1, B), dim3(dpf::kEvalBlock), 0, st, n, (int64_t)ld, vm, va,
+                       bus_type, Vw, m_res);
     hipLaunchKernelGGL(dpf::forward_kernel, dim3(nblk, B), dim3(dpf::kEvalBlock), 0, st, n, g->row_ptr, g->col_idx,
                        (const double2 *)g->val, bus_type, (const double2 *)s_spec, (int64_t)s_ld, ov, Vw, m_res,
                        (int64_t)ld, (double2 *)nullptr, ww, aI, part, (double2 *)g_s);
@@ -1021,8 +1074,7 @@ int dpf_param_grad(const dpf_grid_t *g, int32_t B, int32_t ld, const int8_t *bus
                            Vw, ww, (int64_t)bld, g_r, g_x, g_b);
     }
     if (loss)
-        hipLaunchKernelGGL(dpf::finalize_kernel, dim3((B + 255) / 256), dim3(256), 0, st, B, nblk, part, m_res,
-                           loss, max_mis);
+        hipLaunchKernelGGL(dpf::finalize_kernel, dim3(B), dim3(dpf::kWave), 0, st, nblk, part, m_res, loss, max_mis);
     DPF_HIP(hipGetLastError());
     return DPF_OK;
 }
@@ -1546,14 +1598,12 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
         double *m_res = lossv + align_up(sizeof(double) * (size_t)B, 256) / sizeof(double);
         double2 *Vw = a.scratch, *ww = a.scratch + a.st_stride, *aIw = a.scratch + 2 * a.st_stride;
         double2 *part = (double2 *)(ws + L.off_part);  // B x slices >= B x nblk entries
-        hipLaunchKernelGGL(dpf::residual_count_kernel, dim3(1), dim3(1024), 0, st, n, bus_type, m_res);
-        hipLaunchKernelGGL(dpf::polar_kernel, dim3(nblk, B), dim3(dpf::kEvalBlock), 0, st, n, (int64_t)ld, vm, va,
-                           Vw);
+        hipLaunchKernelGGL(dpf::polar_kernel, dim3(nblk + 1, B), dim3(dpf::kEvalBlock), 0, st, n, (int64_t)ld, vm, va,
+                           bus_type, Vw, m_res);
         hipLaunchKernelGGL(dpf::forward_kernel, dim3(nblk, B), dim3(dpf::kEvalBlock), 0, st, n, g->row_ptr,
                            g->col_idx, (const double2 *)g->val, bus_type, (const double2 *)s_spec, (int64_t)s_ld,
                            a.ov, Vw, m_res, (int64_t)ld, (double2 *)nullptr, ww, aIw, part, (double2 *)nullptr);
-        hipLaunchKernelGGL(dpf::finalize_kernel, dim3((B + 255) / 256), dim3(256), 0, st, B, nblk, part, m_res, lossv,
-                           key);
+        hipLaunchKernelGGL(dpf::finalize_kernel, dim3(B), dim3(dpf::kWave), 0, st, nblk, part, m_res, lossv, key);
         hipLaunchKernelGGL(dpf::rank_desc_kernel, dim3((B + 255) / 256), dim3(256), 0, st, B, key, order);
         DPF_HIP(hipGetLastError());
         a.order = order;

@@ -119,3 +119,57 @@ def test_resident_solves_above_the_register_kernels(dpf, n, m, hub):
         assert np.abs(va[c].cpu().numpy() - ref["va"]).max() < TOL, c
     fixed = cu(g.bus_type != 0, torch.bool)
     assert (state[0][:, fixed] == 0).all() and (state[2][:, fixed] == 0).all()
+
+
+@pytest.mark.parametrize("n,m,B", [(2, 1, 2), (64, 100, 3), (65, 99, 2), (256, 380, 2), (257, 390, 2), (1024, 1500, 2),
+                                   (1025, 1500, 2), (2048, 3000, 2), (2049, 3000, 3), (2049, 3000, 64),
+                                   (5121, 7300, 64), (10176, 14500, 64), (10300, 14700, 64)])
+def test_evaluation_by_case_and_by_bus(dpf, n, m, B):
+    """dpf_mismatch_grad at the edges of its kernels (rows per thread of the
+    one-workgroup-per-case form, its largest grid, one bus-per-thread form beyond it
+    and for few cases of large grids), with a hub row, an outage, per-case injections
+    and angles beyond pi/4; and without outputs that are not asked for."""
+    rng = np.random.default_rng(43000 + n + B)
+    g = random_grid(rng, n, m, min(70, n // 3))
+    S0 = oracle.injections(oracle.ybus_of(g), g.vm, g.va)
+    S = S0[None] * rng.uniform(0.9, 1.1, (B, n))
+    vm = g.vm[None] + rng.normal(0, 1e-2, (B, n))
+    va = g.va[None] + rng.normal(0, 1e-2, (B, n))
+    va[1] += 2.5
+    nbr = synth.non_bridge_branches(n, g.f, g.t)
+    outage = np.full(B, -1, np.int32)
+    if len(nbr):
+        outage[1] = nbr[len(nbr) // 2]
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    args = (Yg, g.bus_type, cu(S, torch.complex128), cu(vm), cu(va))
+    r = dpf.mismatch_grad(*args, outage=cu(outage, torch.int32))
+    for c in sorted({0, 1, B - 1}):
+        Yo = oracle.ybus_of(g, skip=int(outage[c]))
+        loss, mu, gv, ga = oracle.loss_grad(Yo, g.bus_type, vm[c], va[c], S[c])
+        dS = oracle.injections(Yo, vm[c], va[c]) - S[c]
+        assert abs(r["loss"][c].item() - loss) <= TOL * loss
+        assert abs(r["max_mis"][c].item() - mu) <= TOL * mu
+        for x, ref in ((r["dS"], dS), (r["g_vm"], gv), (r["g_va"], ga)):
+            assert np.abs(x[c].cpu().numpy() - ref).max() <= TOL * max(np.abs(ref).max(), 1e-300), c
+    few = dpf.mismatch_grad(*args, outage=cu(outage, torch.int32), want_dS=False, want_grad=False)
+    assert torch.equal(few["loss"], r["loss"]) and torch.equal(few["max_mis"], r["max_mis"])
+
+
+@pytest.mark.parametrize("n,m", [(2049, 3000), (5080, 7300)])
+def test_branch_gradients_by_case_and_by_bus(dpf, n, m):
+    """dpf_param_grad of the same case alone (one thread per bus) and in a batch of 64
+    (one workgroup per case) agrees; the branch that is out gets 0."""
+    rng = np.random.default_rng(44000 + n)
+    g = random_grid(rng, n, m, 20)
+    S = oracle.injections(oracle.ybus_of(g), g.vm, g.va) * 0.97
+    vm = cu(np.tile(g.vm + rng.normal(0, 1e-2, n), (64, 1)))
+    va = cu(np.tile(g.va + rng.normal(0, 1e-2, n), (64, 1)))
+    out = cu(np.full(64, synth.non_bridge_branches(n, g.f, g.t)[0]), torch.int32)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    one = dpf.param_grad(Yg, g.bus_type, cu(S, torch.complex128), vm[:1], va[:1], outage=out[:1])
+    many = dpf.param_grad(Yg, g.bus_type, cu(S, torch.complex128), vm, va, outage=out)
+    for k in ("loss", "max_mis", "g_r", "g_x", "g_b", "g_s"):
+        a, b = one[k][0].cpu().numpy(), many[k].cpu().numpy()
+        for c in (0, 63):
+            assert np.abs(a - b[c]).max() <= TOL * max(np.abs(a).max(), 1e-300), (k, c)
+    assert (many["g_r"][:, out[0].item()] == 0).all() and (one["g_x"][:, out[0].item()] == 0).all()
