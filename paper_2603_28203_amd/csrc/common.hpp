@@ -135,11 +135,11 @@ __device__ __forceinline__ double uniform(double x) {
     const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
-// the last lane's value in every lane (scalar registers)
-__device__ __forceinline__ double last_lane(double x) {
+// one lane's value in every lane (scalar registers)
+__device__ __forceinline__ double read_lane(double x, int lane) {
     const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffLL), kWave - 1);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), kWave - 1);
+    const int lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffLL), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 // Device-scope (relaxed agent-scope atomic) store and load of a double: the store

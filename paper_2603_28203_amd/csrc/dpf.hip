@@ -104,6 +104,9 @@ int device_info(DeviceInfo &out) {
 
 constexpr int kGfx950LdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
 
+// Bytes of static LDS of the DC kernel besides its dynamic array.
+constexpr int kDcStaticLds = 2 * 16 * 16 + 2 * 4 * (dpf::kDcMaxRows / dpf::kWave) + 256;
+
 // Bytes of static LDS the solve kernels use besides the dynamic exchange array.
 constexpr int kSolveStaticLds = 2 * (1024 / dpf::kWave) * 8 + 256;
 
@@ -1123,6 +1126,32 @@ int dpf_dc_init(const dpf_grid_t *g_dc, int32_t B, int32_t ld, const int8_t *bus
     a.iters = iters;
     a.res_out = residual;
     hipStream_t st = (hipStream_t)stream;
+    if (n <= dpf::kDcMaxRows) {
+        struct Shape {
+            int nt, k;
+            void (*fn)(dpf::DcArgs, int32_t);
+        };
+        static const Shape shapes[] = {
+            {64, 1, dpf::dc_cg_kernel<64, 1, 8>},     {128, 1, dpf::dc_cg_kernel<128, 1, 8>},
+            {256, 1, dpf::dc_cg_kernel<256, 1, 8>},   {512, 1, dpf::dc_cg_kernel<512, 1, 8>},
+            {512, 2, dpf::dc_cg_kernel<512, 2, 8>},   {512, 3, dpf::dc_cg_kernel<512, 3, 8>},
+            {512, 4, dpf::dc_cg_kernel<512, 4, 8>},   {512, 6, dpf::dc_cg_kernel<512, 6, 8>},
+            {512, 8, dpf::dc_cg_kernel<512, 8, 4>},   {1024, 8, dpf::dc_cg_kernel<1024, 8, 0>},
+        };
+        const Shape *s = shapes;
+        while (n > s->nt * s->k) ++s;
+        // LDS: the direction and as many of the entries the grid can have as fit (the
+        // kernel reads the CSR when its slices need more)
+        const int64_t wmax = g_dc->max_row_nnz > 0 ? g_dc->max_row_nnz : std::max<int32_t>(g_dc->nnz, 1);
+        const int64_t bound = std::min<int64_t>((n + 63) / 64 * 64 * wmax, (int64_t)64 * std::max<int32_t>(g_dc->nnz, 1));
+        const int64_t room = ((int64_t)dev.lds_per_block - kDcStaticLds - 8 * (int64_t)n) / 10 / 64 * 64;
+        const int64_t cap = std::max<int64_t>(0, std::min(bound, room));
+        const int bytes = (int)(8 * (int64_t)n + 10 * cap);
+        DPF_HIP(hipFuncSetAttribute((const void *)s->fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+        hipLaunchKernelGGL(s->fn, dim3(B), dim3(s->nt), (size_t)bytes, st, a, (int32_t)cap);
+        DPF_HIP(hipGetLastError());
+        return DPF_OK;
+    }
     DPF_HIP(hipFuncSetAttribute((const void *)dpf::dc_pcg_kernel<1024>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds));
     hipLaunchKernelGGL(dpf::dc_pcg_kernel<1024>, dim3(B), dim3(1024), lds, st, a);

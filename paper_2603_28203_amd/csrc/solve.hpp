@@ -589,8 +589,8 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
             __syncthreads();
             if constexpr (NW == 1) {  // one wave: its last lane holds the item's sums
                 wave_last_sum_max(lsum, lmax);
-                lsum = last_lane(lsum);
-                lmax = last_lane(lmax);
+                lsum = read_lane(lsum, kWave - 1);
+                lmax = read_lane(lmax, kWave - 1);
             }
 
             // ---------------- B: adjoint product and gradients (they change no state yet)

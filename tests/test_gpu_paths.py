@@ -173,3 +173,25 @@ def test_branch_gradients_by_case_and_by_bus(dpf, n, m):
         for c in (0, 63):
             assert np.abs(a - b[c]).max() <= TOL * max(np.abs(a).max(), 1e-300), (k, c)
     assert (many["g_r"][:, out[0].item()] == 0).all() and (one["g_x"][:, out[0].item()] == 0).all()
+
+
+@pytest.mark.parametrize("n,m,hub", [(2, 1, 0), (64, 90, 40), (65, 90, 9), (513, 760, 30), (1537, 2300, 12),
+                                     (3072, 4400, 0), (3073, 4400, 20), (4097, 5900, 10), (8193, 11800, 0)])
+def test_dc_start_at_its_size_edges(dpf, n, m, hub):
+    """dpf_dc_init at the edges of its kernels (rows per thread, rows longer than the
+    entries kept in registers, the largest register form and the form beyond it), with
+    a non-zero slack angle and an outage, against the oracle's direct solve."""
+    rng = np.random.default_rng(45000 + n)
+    g = random_grid(rng, n, m, hub)
+    S = rng.normal(0, 0.1, (3, n)) + 0j
+    nbr = synth.non_bridge_branches(n, g.f, g.t)
+    outage = np.array([-1, nbr[0] if len(nbr) else -1, -1], np.int32)
+    va0 = np.zeros((3, n))
+    va0[:, g.slack] = 0.25
+    va = cu(va0)
+    Yg = dpf.build_dc_grid(n, g.f, g.t, g.x)
+    r = dpf.dc_init(Yg, g.bus_type, cu(S, torch.complex128), va, outage=cu(outage, torch.int32), tol=1e-13)
+    assert (r["residual"] <= 1e-13).all()
+    for c in range(3):
+        ref = oracle.dc_power_flow(g, g.bus_type, S[c], va_slack=0.25, skip=int(outage[c]))
+        assert np.abs(va[c].cpu().numpy() - ref).max() <= 1e-9 * max(1.0, np.abs(ref).max()), c
