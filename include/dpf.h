@@ -27,7 +27,7 @@
  *    has been enqueued, except for DPF_EHIP, which reports a HIP runtime
  *    failure (the stream may then hold partial work).
  *  - Scratch memory: the solve and the gradient evaluation take a caller
- *    workspace (query its size first); dpf_build_ybus allocates and frees its
+ *    workspace (query its size first); dpf_build_ybus may allocate and free its
  *    own temporaries.  Nothing else is allocated per call.
  */
 #ifndef DPF_H
@@ -150,8 +150,10 @@ const char *dpf_version(void);
  *   max_row_nnz_out   : host out (nullable): the longest row, for dpf_grid_t.max_row_nnz
  * Errors: DPF_EINVAL for n_bus <= 0, n_branch < 0, a bus index out of range,
  * from == to, or r = x = 0 (detected on the device); DPF_ECAP if the result
- * does not fit (nnz_out still receives the needed size).  Temporaries are
- * allocated with hipMalloc and freed before the call returns.
+ * does not fit (nnz_out still receives the needed size).  Temporaries of up to 16 MiB
+ * sit in the library's static array (see dpf_build_ybus_noalloc) unless another call is
+ * using it; otherwise they are allocated with hipMalloc and freed before the call
+ * returns.
  */
 int dpf_build_ybus(int32_t n_bus, int32_t n_branch, const int32_t *from, const int32_t *to,
                    const double *r, const double *x, const double *b, int32_t nnz_cap,
@@ -167,11 +169,10 @@ int dpf_build_ybus(int32_t n_bus, int32_t n_branch, const int32_t *from, const i
  * grid take 16 (n_bus + 1) + 256 + 8 (n_bus + 2 n_branch) + 16 n_bus bytes, each
  * part rounded up to 256; a grid that needs more than 16 MiB (for example more
  * than about 260 000 buses at 1.5 branches per bus) is rejected with DPF_EINVAL
- * before any device work.  Every call on one device shares that device's array:
- * calls that overlap on one device (two host threads, or two streams) race and
- * must be serialised by the caller; the call returns with `stream` synchronised,
- * so calls made one after the other never overlap.  The array is cleared at the
- * start of each call; nothing of a previous call's contents is used.
+ * before any device work.  Every call on one device shares that device's array;
+ * calls from several host threads take turns, and each returns with `stream`
+ * synchronised, so uses never overlap.  Nothing of a previous call's contents is
+ * used.
  */
 int dpf_build_ybus_noalloc(int32_t n_bus, int32_t n_branch, const int32_t *from, const int32_t *to,
                            const double *r, const double *x, const double *b, int32_t nnz_cap,

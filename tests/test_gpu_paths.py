@@ -195,3 +195,70 @@ def test_dc_start_at_its_size_edges(dpf, n, m, hub):
     for c in range(3):
         ref = oracle.dc_power_flow(g, g.bus_type, S[c], va_slack=0.25, skip=int(outage[c]))
         assert np.abs(va[c].cpu().numpy() - ref).max() <= 1e-9 * max(1.0, np.abs(ref).max()), c
+
+
+@pytest.mark.parametrize("n,hub,twins", [(1, 0, 0), (2, 0, 3), (128, 15, 4), (129, 16, 9), (3000, 900, 200),
+                                         (32768, 40, 500), (32769, 17, 500), (300000, 300, 2000)])
+def test_ybus_build_at_its_size_edges(dpf, n, hub, twins):
+    """dpf_build_ybus at the edges of its kernels (rows sorted in LDS or in place, one
+    workgroup or several for the slots, the totals added up or scanned, the static
+    array or memory of its own), with a hub row and parallel branches in both
+    directions: pattern exact, values to the rounding of their sums (1e-15 relative to the
+    row's largest entry, which the branch-order sums keep)."""
+    rng = np.random.default_rng(46000 + n)
+    k = np.arange(1, n)
+    f = np.concatenate([k - 1 - rng.integers(0, np.minimum(k, 7)), np.zeros(hub, np.int64)]).astype(np.int32)
+    t = np.concatenate([k, 1 + rng.choice(max(1, n - 1), size=hub, replace=False)]).astype(np.int32)
+    if n > 1 and twins:
+        pick = rng.integers(0, len(f), twins)
+        f, t = np.concatenate([f, t[pick]]), np.concatenate([t, f[pick]])
+    m = len(f)
+    r, x, b = rng.uniform(0.01, 0.1, m), rng.uniform(0.05, 0.3, m), rng.uniform(0, 0.05, m)
+    y, ysh = 1.0 / (r + 1j * x), 0.5j * b
+    d = np.arange(n, dtype=np.int64)
+    f64, t64 = f.astype(np.int64), t.astype(np.int64)
+    key = np.concatenate([d * n + d, f64 * n + f64, t64 * n + t64, f64 * n + t64, t64 * n + f64])
+    u, at = np.unique(key, return_inverse=True)
+    v = np.concatenate([np.zeros(n), y + ysh, y + ysh, -y, -y])
+    ref = np.bincount(at, v.real, len(u)) + 1j * np.bincount(at, v.imag, len(u))
+    Y = dpf.build_ybus(n, f, t, r, x, b)
+    ptr = np.searchsorted(u // n, np.arange(n + 1))
+    assert Y.nnz == len(u) and Y.max_row_nnz == np.diff(ptr).max()
+    assert np.array_equal(Y.row_ptr.cpu().numpy(), ptr) and np.array_equal(Y.col_idx.cpu().numpy(), u % n)
+    scale = np.maximum.reduceat(np.abs(ref), ptr[:-1])[u // n]
+    assert (np.abs(Y.val.cpu().numpy() - ref) <= 1e-15 * np.maximum(scale, np.abs(ref)) * np.sqrt(1 + hub)).all()
+    if n > 1:  # too small a capacity: the needed size is reported, no entry is written
+        import ctypes
+        col = torch.full((Y.nnz,), -7, dtype=torch.int32, device="cuda")
+        val = torch.full((Y.nnz,), 5.0, dtype=torch.complex128, device="cuda")
+        row = torch.empty(n + 1, dtype=torch.int32, device="cuda")
+        nnz, mx = ctypes.c_int32(0), ctypes.c_int32(0)
+        rc = dpf.lib().dpf_build_ybus(n, m, *(ctypes.c_void_p(z.data_ptr()) for z in (Y.f, Y.t, Y.r, Y.x, Y.b)),
+                                      Y.nnz - 1, *(ctypes.c_void_p(z.data_ptr()) for z in (row, col, val)),
+                                      ctypes.byref(nnz), ctypes.byref(mx),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == dpf.binding.DPF_ECAP and nnz.value == Y.nnz
+        assert (col == -7).all() and (val == 5.0).all()
+
+
+def test_ybus_builds_from_several_threads(dpf):
+    """Overlapping builds on one device (the static array is used by one at a time, the
+    allocating call falls back to memory of its own) all give the grid's own matrix."""
+    import threading
+    grids = [random_grid(np.random.default_rng(47000 + k), 500 + 300 * k, 800 + 450 * k) for k in range(4)]
+    want = [dpf.build_ybus(g.n_bus, g.f, g.t, g.r, g.x, g.b) for g in grids]
+    bad = []
+
+    def work(k):
+        g = grids[k]
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for i in range(20):
+                Y = dpf.build_ybus(g.n_bus, g.f, g.t, g.r, g.x, g.b, noalloc=(i + k) % 2 == 0)
+                torch.cuda.current_stream().synchronize()
+                if not (torch.equal(Y.col_idx, want[k].col_idx) and torch.equal(Y.val, want[k].val)):
+                    bad.append((k, i))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert not bad
