@@ -1521,7 +1521,7 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
     double2 *sval = (double2 *)(ws + L.off_val);
     int32_t *sub_bw = (int32_t *)(ws + L.off_bw);
     const int32_t wmax = g->max_row_nnz > 0 ? g->max_row_nnz : std::max<int32_t>(g->nnz, 1);
-    if (done_ns) hipLaunchKernelGGL(dpf::stamp_kernel, dim3(1), dim3(64), 0, st, (int64_t *)(ws + 8));
+    int64_t *stamp = done_ns ? (int64_t *)(ws + 8) : nullptr;  // written by the first kernel of the call
     // the register kernels' copy has its rows sorted by length (one slice has nothing to sort)
     int32_t *srow = nullptr, *sslot = nullptr;
     if (L.off_row && L.n_slices > 1 && v->mode == dpf::kReg && !plan.teams && !has_wide) {
@@ -1533,18 +1533,22 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
     if (n_sub <= dpf::kSellSmallSubs && L.n_slices <= dpf::kSellSmallSlices) {  // small grids: one launch
         hipLaunchKernelGGL(dpf::sell_small_kernel, dim3(1), dim3(dpf::kSellSmallThreads), 0, st, n_sub,
                            sub_offset_dev, g->n_bus, g->row_ptr, g->col_idx, (const double2 *)g->val, wmax, nslice,
-                           slice_off, width, start, scol, sval, sub_bw, bad, bad + 4, srow, sslot);
+                           slice_off, width, start, scol, sval, sub_bw, bad, bad + 4, srow, sslot, stamp);
     } else {
-        hipLaunchKernelGGL(dpf::sell_count_kernel, dim3((n_sub + 255) / 256), dim3(256), 0, st, n_sub,
-                           sub_offset_dev, g->n_bus, nslice, sub_bw, bad, bad + 4);  // clears header words 0, 4 and 5
-        hipLaunchKernelGGL(dpf::scan_kernel, dim3(1), dim3(1024), 0, st, n_sub, nslice, 0, slice_off);
+        const int cblk = (n_sub + dpf::kSellCountThreads - 1) / dpf::kSellCountThreads;
+        hipLaunchKernelGGL(dpf::sell_count_kernel, dim3(cblk), dim3(dpf::kSellCountThreads), 0, st, n_sub,
+                           sub_offset_dev, g->n_bus, nslice, slice_off, sub_bw, bad, bad + 4,
+                           stamp);  // clears header words 0, 4 and 5
+        if (cblk > 1)
+            hipLaunchKernelGGL(dpf::scan_kernel, dim3(1), dim3(1024), 0, st, n_sub, nslice, 0, slice_off);
         if (L.n_slices > 0) {
             hipLaunchKernelGGL(dpf::sell_width_kernel, dim3(L.n_slices), dim3(dpf::kWave), 0, st, n_sub,
                                sub_offset_dev, g->n_bus, slice_off, g->row_ptr, wmax, width, bad);
             hipLaunchKernelGGL(dpf::scan_kernel, dim3(1), dim3(1024), 0, st, L.n_slices, width, 0, start);
-            hipLaunchKernelGGL(dpf::sell_fill_kernel, dim3(L.n_slices), dim3(dpf::kWave), 0, st, n_sub,
-                               sub_offset_dev, g->n_bus, slice_off, g->row_ptr, g->col_idx, (const double2 *)g->val,
-                               width, start, scol, sval, sub_bw);
+            constexpr int kPer = dpf::kSellFillThreads / dpf::kWave;
+            hipLaunchKernelGGL(dpf::sell_fill_kernel, dim3((L.n_slices + kPer - 1) / kPer), dim3(dpf::kSellFillThreads),
+                               0, st, L.n_slices, n_sub, sub_offset_dev, g->n_bus, slice_off, g->row_ptr, g->col_idx,
+                               (const double2 *)g->val, width, start, scol, sval, sub_bw);
         }
     }
     // cases with an outage index that is neither -1 nor a branch (after the header is cleared)

@@ -29,23 +29,44 @@ struct SellView {
     const int32_t *slot;       // [n_bus]
 };
 
-// slices per sub-grid: ceil(n_s / 64); clears the per-sub-grid bandwidth
-// (thread 0 also clears the bad-grid flag and the two header words at `queue`,
-// the second of which counts finished items for the tail handoff)
-__global__ void sell_count_kernel(int32_t n_sub, const int32_t *__restrict__ sub_off, int32_t n_bus,
-                                  int32_t *__restrict__ nslice, int32_t *__restrict__ bw, int32_t *__restrict__ bad,
-                                  int32_t *__restrict__ queue) {
-    int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
+// slices per sub-grid: ceil(n_s / 64); clears the per-sub-grid bandwidth, the bad-grid
+// flag and the two header words at `queue` (the second counts finished items for the tail
+// handoff), and stamps the start of the call's kernels (stamp may be null).  With at
+// most one workgroup's sub-grids it also scans the counts into slice_off.
+constexpr int kSellCountThreads = 1024;
+__global__ __launch_bounds__(kSellCountThreads) void sell_count_kernel(
+    int32_t n_sub, const int32_t *__restrict__ sub_off, int32_t n_bus, int32_t *__restrict__ nslice,
+    int32_t *__restrict__ slice_off, int32_t *__restrict__ bw, int32_t *__restrict__ bad, int32_t *__restrict__ queue,
+    int64_t *__restrict__ stamp) {
+    __shared__ int32_t part[kSellCountThreads / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int32_t s = blockIdx.x * kSellCountThreads + tid;
     if (s == 0) {
+        if (stamp) *stamp = wall_clock64();
         *bad = 0;
         queue[0] = 0;
         queue[1] = 0;
     }
-    if (s >= n_sub) return;
-    int32_t lo = sub_off ? sub_off[s] : 0;
-    int32_t hi = sub_off ? sub_off[s + 1] : n_bus;
-    nslice[s] = (hi - lo + kWave - 1) / kWave;
-    bw[s] = 0;
+    int32_t ns = 0;
+    if (s < n_sub) {
+        const int32_t lo = sub_off ? sub_off[s] : 0;
+        const int32_t hi = sub_off ? sub_off[s + 1] : n_bus;
+        ns = (hi - lo + kWave - 1) / kWave;
+        nslice[s] = ns;
+        bw[s] = 0;
+    }
+    if (gridDim.x > 1) return;
+    int32_t incl = ns;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t y = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += y;
+    }
+    if (lane == kWave - 1) part[wv] = incl;
+    __syncthreads();
+    for (int k = 0; k < wv; ++k) incl += part[k];
+    if (s < n_sub) slice_off[s] = incl - ns;
+    if (s == n_sub - 1) slice_off[n_sub] = incl;
 }
 
 __device__ __forceinline__ int32_t find_sub(int32_t g, int32_t n_sub, const int32_t *__restrict__ slice_off) {
@@ -84,19 +105,27 @@ __device__ __forceinline__ int32_t slice_fill(int32_t r, int32_t lo, int32_t hi,
     int32_t len = r < hi ? rp[r + 1] - q0 : 0;
     int32_t own = r < hi ? r - lo : 0;
     int32_t far = 0;
-    for (int32_t k = 0; k < w; ++k) {
-        int32_t c = own;
-        double2 v = make_double2(0.0, 0.0);
-        if (k < len) {
-            int32_t j = ci[q0 + k];
-            if (j >= lo && j < hi) {
-                c = j - lo;
-                v = yv[q0 + k];
-                far = max(far, abs(c - own));
-            }
+    // groups of four entries, whose loads are issued together (past the row's end its
+    // first entry is loaded again; a row has at least one where it has any)
+    for (int32_t k0 = 0; k0 < w; k0 += 4) {
+        int32_t j[4];
+        double2 y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t q = q0 + (k0 + u < len ? k0 + u : 0);
+            j[u] = len > 0 ? ci[q] : -1;
+            y[u] = len > 0 ? yv[q] : make_double2(0.0, 0.0);
         }
-        col[base + k * kWave] = slot ? slot[c] : c;
-        val[base + k * kWave] = v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t k = k0 + u;
+            if (k >= w) break;
+            const bool in = k < len && j[u] >= lo && j[u] < hi;
+            const int32_t c = in ? j[u] - lo : own;
+            if (in) far = max(far, abs(c - own));
+            col[base + k * kWave] = slot ? slot[c] : c;
+            val[base + k * kWave] = in ? y[u] : make_double2(0.0, 0.0);
+        }
     }
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) far = max(far, __shfl_xor(far, o, kWave));
@@ -117,22 +146,40 @@ __global__ __launch_bounds__(kWave) void sell_width_kernel(int32_t n_sub, const 
     if (threadIdx.x == 0) width[g] = len;
 }
 
-__global__ __launch_bounds__(kWave) void sell_fill_kernel(int32_t n_sub, const int32_t *__restrict__ sub_off,
-                                                          int32_t n_bus, const int32_t *__restrict__ slice_off,
-                                                          const int32_t *__restrict__ rp,
-                                                          const int32_t *__restrict__ ci,
-                                                          const double2 *__restrict__ yv,
-                                                          const int32_t *__restrict__ width,
-                                                          const int32_t *__restrict__ start,
-                                                          int32_t *__restrict__ col, double2 *__restrict__ val,
-                                                          int32_t *__restrict__ bw) {
-    int32_t g = blockIdx.x;
-    int32_t s = find_sub(g, n_sub, slice_off);
-    int32_t lo = sub_off ? sub_off[s] : 0;
-    int32_t hi = sub_off ? sub_off[s + 1] : n_bus;
-    int32_t r = lo + (g - slice_off[s]) * kWave + threadIdx.x;
-    const int32_t far = slice_fill(r, lo, hi, width[g], start[g] * kWave + threadIdx.x, rp, ci, yv, col, val);
-    if (threadIdx.x == 0) atomicMax(&bw[s], far);
+// one wave per slice.  The bandwidths of all sub-grids share a cache line or two, on
+// which device-wide atomics go one after the other (58 us for 5300 slices with one
+// each), so the slices of a workgroup that lie in one sub-grid make one between them.
+constexpr int kSellFillThreads = 512;
+__global__ __launch_bounds__(kSellFillThreads) void sell_fill_kernel(
+    int32_t n_slices, int32_t n_sub, const int32_t *__restrict__ sub_off, int32_t n_bus,
+    const int32_t *__restrict__ slice_off, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+    const double2 *__restrict__ yv, const int32_t *__restrict__ width, const int32_t *__restrict__ start,
+    int32_t *__restrict__ col, double2 *__restrict__ val, int32_t *__restrict__ bw) {
+    constexpr int NW = kSellFillThreads / kWave;
+    __shared__ int32_t wfar[NW], wsub[NW];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int32_t g = blockIdx.x * NW + wv;
+    int32_t far = 0, s = -1;
+    if (g < n_slices) {
+        s = find_sub(g, n_sub, slice_off);
+        const int32_t lo = sub_off ? sub_off[s] : 0;
+        const int32_t hi = sub_off ? sub_off[s + 1] : n_bus;
+        const int32_t r = lo + (g - slice_off[s]) * kWave + lane;
+        far = slice_fill(r, lo, hi, width[g], start[g] * kWave + lane, rp, ci, yv, col, val);
+    }
+    if (lane == 0) {
+        wfar[wv] = far;
+        wsub[wv] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < NW; ++k) {  // runs of equal sub-grids
+            int32_t m = wfar[k];
+            const int32_t t = wsub[k];
+            for (; k + 1 < NW && wsub[k + 1] == t; ++k) m = max(m, wfar[k + 1]);
+            if (t >= 0 && m > 0) atomicMax(&bw[t], m);
+        }
+    }
 }
 
 // The whole build above (counts, the two scans, widths, entries) in one
@@ -197,7 +244,7 @@ __global__ __launch_bounds__(kSellSmallThreads) void sell_small_kernel(
     const int32_t *__restrict__ ci, const double2 *__restrict__ yv, int32_t max_w, int32_t *__restrict__ nslice,
     int32_t *__restrict__ slice_off, int32_t *__restrict__ width, int32_t *__restrict__ start,
     int32_t *__restrict__ col, double2 *__restrict__ val, int32_t *__restrict__ bw, int32_t *__restrict__ bad,
-    int32_t *__restrict__ queue, int32_t *row, int32_t *slot) {
+    int32_t *__restrict__ queue, int32_t *row, int32_t *slot, int64_t *__restrict__ stamp) {
     __shared__ uint16_t sort_cnt[kSellSortKeys][kSellSmallThreads];
     __shared__ int32_t soff[kSellSmallSubs + 1];
     __shared__ int32_t wsh[kSellSmallSlices];       // widths
@@ -207,6 +254,7 @@ __global__ __launch_bounds__(kSellSmallThreads) void sell_small_kernel(
     const int lane = tid & (kWave - 1), wv = tid / kWave;
     constexpr int kWaves = kSellSmallThreads / kWave;
     if (tid == 0) {
+        if (stamp) *stamp = wall_clock64();  // the start of the call's kernels
         *bad = 0;
         queue[0] = 0;
         queue[1] = 0;

@@ -1355,9 +1355,4 @@ __global__ void rank_desc_kernel(int32_t B, const double *__restrict__ key, int3
     order[rank] = i;
 }
 
-// wall-clock stamp at the start of a solve call (for per-item completion times)
-__global__ void stamp_kernel(int64_t *stamp) {
-    if (threadIdx.x == 0) *stamp = wall_clock64();
-}
-
 }  // namespace dpf

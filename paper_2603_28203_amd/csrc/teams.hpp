@@ -72,7 +72,7 @@ namespace dpf {
 // (measured on 64 cases of 9241 buses, 256 cases of 3000 and the uneven batch).
 // The gathers unroll by 2 (by 4: 44 spilled registers and 5-10% slower).
 constexpr int kTeamThreads = 1024;
-constexpr int kPlanThreads = 256;
+constexpr int kPlanThreads = 512;
 // members per team at most: one 9241-bus case takes 14 us per iteration on 32
 // members, 19 us on 128 (more arrivals per barrier, more halo per row)
 constexpr int kTeamMaxMembers = 32;
@@ -118,63 +118,109 @@ __device__ __forceinline__ int load_key(int L) {
     return min(kLoadKeys - 1, 2 * lg + half);
 }
 
-template <int NT>
-__device__ __forceinline__ long long block_sum_ll(long long v, long long *buf) {
-    buf[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = NT / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) buf[threadIdx.x] += buf[threadIdx.x + o];
-        __syncthreads();
-    }
-    const long long r = buf[0];
-    __syncthreads();
-    return r;
-}
+// One wave per number of waves w searches its own row target without a barrier (all
+// eight searches one after the other with block-wide sums took 76 us for one grid, 6% of
+// a 100-iteration solve; this kernel 5).
+static_assert(kPlanThreads == kTeamMaxWaves * kWave, "one wave per w");
 
 __global__ __launch_bounds__(kPlanThreads) void team_plan_kernel(int32_t n_sub, const int32_t *__restrict__ sub_off,
                                                                  int32_t n_bus, const int32_t *__restrict__ sub_bw,
                                                                  int32_t B, TeamArgs p) {
     __shared__ int32_t cnt[kLoadKeys][kPlanThreads];
     __shared__ int32_t wtot[kPlanThreads / kWave][kLoadKeys];
-    __shared__ long long buf[kPlanThreads];
-    __shared__ int32_t sh_R;
+    __shared__ long long wsum[kPlanThreads / kWave];
+    __shared__ long long sh_cost[kTeamMaxWaves];
+    __shared__ int32_t sh_R[kTeamMaxWaves];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave;
     auto n_of = [&](int s) { return sub_off ? sub_off[s + 1] - sub_off[s] : n_bus; };
+    auto wave_sum_ll = [](long long v) {
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+        return v;
+    };
+    // members of all items at row target R, in every lane of the wave
     auto members = [&](int R) {
         long long m = 0;
-        for (int s = tid; s < n_sub; s += kPlanThreads) m += team_size(n_of(s), sub_bw[s], R, p.win, p.tmax);
-        return block_sum_ll<kPlanThreads>(m, buf) * B;
+        for (int s = lane; s < n_sub; s += kWave) m += team_size(n_of(s), sub_bw[s], R, p.win, p.tmax);
+        return wave_sum_ll(m) * B;
     };
 
     // ---- per-member row target
     const long long total = (long long)B * n_bus;
     const int rcap = max(kWave, (p.win / kWave) * kWave);
-    int bestR = rcap;
-    long long best = -1;
-    for (int w = 1; w <= kTeamMaxWaves; ++w) {
+    {
+        const int w = wv + 1;
         const long long cap_m = (long long)w * p.grid;
         const long long need = (total + cap_m - 1) / cap_m;
         int lo = (int)min<long long>(rcap, max<long long>(kWave, (need + kWave - 1) / kWave * kWave));
         int hi = rcap;
-        if (members(hi) > cap_m) continue;  // not even at the largest rows
-        while (lo < hi) {                   // smallest R (multiple of 64) that fits w waves
-            const int mid = (lo / kWave + hi / kWave) / 2 * kWave;
-            if (members(mid) <= cap_m) hi = mid;
-            else lo = mid + kWave;
+        long long cost = -1;                // not even at the largest rows
+        if (members(hi) <= cap_m) {
+            while (lo < hi) {               // smallest R (multiple of 64) that fits w waves
+                const int mid = (lo / kWave + hi / kWave) / 2 * kWave;
+                if (members(mid) <= cap_m) hi = mid;
+                else lo = mid + kWave;
+            }
+            cost = (long long)w * (hi + kTeamRowsPerBarrier);
         }
-        const long long cost = (long long)w * (hi + kTeamRowsPerBarrier);
-        if (best < 0 || cost < best) {
-            best = cost;
-            bestR = hi;
+        if (lane == 0) {
+            sh_cost[wv] = cost;
+            sh_R[wv] = hi;
         }
     }
-    if (tid == 0) sh_R = bestR;
     __syncthreads();
-    const int R = sh_R;
+    int R = rcap;
+    long long best = -1;
+    for (int w = 0; w < kTeamMaxWaves; ++w)
+        if (sh_cost[w] >= 0 && (best < 0 || sh_cost[w] < best)) {
+            best = sh_cost[w];
+            R = sh_R[w];
+        }
 
-    // ---- units in descending per-member load (stable counting sort over the buckets)
+    // ---- units in descending per-member load
     const int items = B * n_sub;
+    for (int u = tid; u < items; u += kPlanThreads) p.bar[(int64_t)u * kTeamBarStride] = 0;
+    if (items <= kPlanThreads) {
+        // one item per thread: its unit is the number of items of a larger bucket or of
+        // the same bucket before it, then a scan of the team sizes in unit order
+        int32_t *key = cnt[0], *size = cnt[1];
+        int T = 0, k = 0;
+        if (tid < items) {
+            const int s = tid / B;
+            const int n = n_of(s);
+            T = team_size(n, sub_bw[s], R, p.win, p.tmax);
+            k = load_key((n + T - 1) / T);
+            key[tid] = k;
+        }
+        __syncthreads();
+        int unit = 0;
+        if (tid < items) {
+            for (int j = 0; j < items; ++j) unit += key[j] > k || (key[j] == k && j < tid) ? 1 : 0;
+            p.unit_item[unit] = tid;
+            size[unit] = T;
+        }
+        __syncthreads();
+        const int own = tid < items ? size[tid] : 0;
+        int incl = own;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += y;
+        }
+        if (lane == kWave - 1) wsum[wv] = incl;
+        __syncthreads();
+        for (int w = 0; w < wv; ++w) incl += (int)wsum[w];
+        if (tid < items) p.first[tid] = incl - own;
+        if (tid == items - 1) {
+            p.first[items] = incl;
+            p.hdr[0] = 0;
+            p.hdr[1] = incl;
+            p.hdr[2] = items;
+        }
+        return;
+    }
+    // more items: stable counting sort over the buckets
     const int per = (items + kPlanThreads - 1) / kPlanThreads;
     const int i0 = min(tid * per, items), i1 = min(i0 + per, items);
     auto key_of = [&](int item) {
@@ -218,6 +264,7 @@ __global__ __launch_bounds__(kPlanThreads) void team_plan_kernel(int32_t n_sub, 
         p.unit_item[cnt[k][tid]] = i;
         cnt[k][tid] += 1;
     }
+    dev_stores_done();
     __syncthreads();
 
     // ---- first ticket of each unit: exclusive scan of the team sizes in unit order
@@ -226,10 +273,16 @@ __global__ __launch_bounds__(kPlanThreads) void team_plan_kernel(int32_t n_sub, 
         const int s = p.unit_item[u] / B;
         own += team_size(n_of(s), sub_bw[s], R, p.win, p.tmax);
     }
-    buf[tid] = own;
+    long long before = own;  // inclusive scan over the wave, then over the waves
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const long long y = __shfl_up(before, o, kWave);
+        if (lane >= o) before += y;
+    }
+    if (lane == kWave - 1) wsum[wv] = before;
     __syncthreads();
-    long long before = 0;
-    for (int k = 0; k < tid; ++k) before += buf[k];
+    before -= own;
+    for (int k = 0; k < wv; ++k) before += wsum[k];
     for (int u = i0; u < i1; ++u) {
         p.first[u] = (int32_t)before;
         const int s = p.unit_item[u] / B;
@@ -241,7 +294,6 @@ __global__ __launch_bounds__(kPlanThreads) void team_plan_kernel(int32_t n_sub, 
         p.hdr[1] = (int32_t)before;
         p.hdr[2] = items;
     }
-    for (int u = tid; u < items; u += kPlanThreads) p.bar[(int64_t)u * kTeamBarStride] = 0;
 }
 
 // Arrival barrier of the T members of one unit; false when it was abandoned.
