@@ -53,8 +53,8 @@ __device__ __forceinline__ double2 cfma(double2 a, double2 b, double2 acc) {
 //    column, and adds nothing);
 //  - otherwise (1024-thread kernels, where other waves hide the gathers and
 //    registers are short): every group predicated, each gather in its own step.
-template <int U, bool JOINT, typename Get>
-__device__ __forceinline__ double2 sell_row(const double2 *__restrict__ val, const int32_t *__restrict__ col,
+template <int U, bool JOINT, typename Col, typename Get>
+__device__ __forceinline__ double2 sell_row(const double2 *__restrict__ val, const Col *__restrict__ col,
                                             int base, int w, int own, Get get, double2 acc) {
     auto group = [&](int q0, auto full) {
         constexpr bool FULL = decltype(full)::value;

@@ -346,7 +346,7 @@ __device__ __forceinline__ bool unit_barrier(long long *cnt, long long target, i
 template <int NT>
 __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &p, int u, int mem, int T,
                                             double2 *__restrict__ X, double (*red)[NT / kWave], int *bar_flag,
-                                            int *scan_part) {
+                                            int *scan_part, int *outside) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int item = p.unit_item[u];
@@ -431,11 +431,15 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
     uint32_t *need = reinterpret_cast<uint32_t *>(X);
     uint16_t *hlist = reinterpret_cast<uint16_t *>(X + p.win);
     const int nwords = (wn + 31) / 32;
+    uint32_t *pre = need + nwords;  // halo columns before each word
     for (int k = tid; k < nwords; k += NT) need[k] = 0u;
+    if (tid == 0) *outside = 0;
     __syncthreads();
     auto mark = [&](int col) {
         const int x = col - xlo;
-        if ((unsigned)x < (unsigned)wn && (col < rlo || col >= rhi)) atomicOr(need + (x >> 5), 1u << (x & 31));
+        if (col >= rlo && col < rhi) return;
+        if ((unsigned)x < (unsigned)wn) atomicOr(need + (x >> 5), 1u << (x & 31));
+        else *outside = 1;
     };
     for (int il = rlo + tid; il < rhi; il += NT) {
         const int gsl = __builtin_amdgcn_readfirstlane(slice0 + (il >> 6));
@@ -466,9 +470,11 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
         }
         if (n_halo <= kTeamHaloCap) {
             int pos = before + incl - cnt_b;
-            for (int w = w0; w < w1; ++w)
+            for (int w = w0; w < w1; ++w) {
+                pre[w] = (uint32_t)pos;
                 for (uint32_t bits = need[w]; bits != 0u; bits &= bits - 1u)
                     hlist[pos++] = (uint16_t)(w * 32 + __ffs(bits) - 1);
+            }
         } else {
             n_halo = -1;
         }
@@ -499,12 +505,53 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
         }
     };
 
+    // Compact form, for members of at most one row per thread where it fits: V and w of
+    // the own rows and the halo columns side by side in LDS (own rows first, then the halo
+    // in list order), the own rows' matrix behind them with its columns renumbered to that
+    // order (16 bits), and a row's state in its thread's registers.  The iterations then
+    // touch global memory for what crosses the barriers only, where the general form's
+    // chain of each sweep went through L2 four to six times.  Members of a team choose it
+    // independently.  us per iteration, general -> compact: 9241 buses, 1 case 10.7 -> 8.6,
+    // 16 cases 13.5 -> 9.7; 3000 buses, 64 cases 12.5 -> 9.5.  (With more rows per thread,
+    // state in memory, it gained nothing: 48 grids 25.4 -> 26.2.  The gathers of a group
+    // issued together spill 118 registers more: 11.7.)
+    const int R = rhi - rlo;
+    const int xc = R + max(n_halo, 0);
+    const int sl0 = slice0 + rlo / kWave;
+    const int e0 = sstart[sl0];
+    const int E = (sstart[slice0 + (rhi + kWave - 1) / kWave] - e0) * kWave;
+    const int mb = max(2 * xc, (nwords * 8 + 15) / 16);  // matrix, in 16-byte units behind X
+    const bool compact = R <= NT && n_halo >= 0 && *outside == 0 && xc < 65536 && (int64_t)mb + (E * 9LL + 7) / 8 <= p.win;
+    double2 *MV = X + mb;
+    uint16_t *MC = reinterpret_cast<uint16_t *>(MV + E);
+    double2 *Xv = X, *Xw = X + xc;
+    int ofc = -1, otc = -1;  // the outage's buses in compact order
+    if (compact) {
+        auto place = [&](int col) -> int {
+            if (col >= rlo && col < rhi) return col - rlo;
+            const int x = col - xlo;
+            if ((unsigned)x >= (unsigned)wn) return 0;  // padding past the sub-grid's end
+            return min(R + (int)pre[x >> 5] + (int)__popc(need[x >> 5] & ((1u << (x & 31)) - 1u)), max(xc - 1, 0));
+        };
+        for (int e = tid; e < E; e += NT) {
+            MV[e] = sval[(int64_t)e0 * kWave + e];
+            MC[e] = (uint16_t)place(scol[(int64_t)e0 * kWave + e]);
+        }
+        if (of >= 0) {
+            ofc = place(of);
+            otc = place(ot);
+        }
+        __syncthreads();  // the bitmap has been read: X is free
+    }
+
     // V of the member's rows for the team
     for (int il = rlo + tid; il < rhi; il += NT) {
         double sn, cs;
         const double2 p0 = P0[il];
         fast_sincos(p0.y, sn, cs);
-        st2(rV, il, make_double2(p0.x * cs, p0.x * sn));
+        const double2 v = make_double2(p0.x * cs, p0.x * sn);
+        st2(rV, il, v);
+        if (compact) Xv[il - rlo] = v;
     }
     long long nbar = 0;
     bool ok = true;
@@ -513,7 +560,116 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
 
     int it = 0, stat = DPF_UNFINISHED;
     double mu = 0.0, loss = 0.0;
-    while (ok) {
+    // team totals: the T partials reduced in the same order by every member (their loads
+    // overlap the refill with w)
+    auto team_totals = [&](double &s, double &m) {
+        s = 0.0;
+        m = 0.0;
+        if (tid < T) {
+            const double2 pp = rsrc_ld2<true>(rPart, tid);
+            s = pp.x;
+            m = pp.y;
+        }
+    };
+    if (compact) {
+        const int il = rlo + tid;  // this thread's row
+        const bool act = il < rhi;
+        double2 p0 = make_double2(0.0, 0.0), p1 = p0, p2 = p0, sp = p0, ai = p0;
+        double cs = 1.0, sn = 0.0;
+        int8_t tk = kSlack;
+        // its slice's width and first entry in LDS (uniform; waves past the rows use the last)
+        const int sl = sl0 + __builtin_amdgcn_readfirstlane(min(tid, max(R - 1, 0)) >> 6);
+        const int w = R > 0 ? swidth[sl] : 0;
+        const int base = R > 0 ? (sstart[sl] - e0) * kWave + lane : 0;
+        if (act) {
+            p0 = P0[il];
+            p1 = P1[il];
+            p2 = P2[il];
+            sp = Sc[il];
+            tk = btp[il];
+            fast_sincos(p0.y, sn, cs);
+        }
+        auto product = [&](const double2 *Z) {
+            double2 acc = sell_row<4, false>(MV, MC, base, w, 0, [&](int q) { return Z[q]; }, make_double2(0.0, 0.0));
+            if (of >= 0) {
+                if (il == of) acc = csub(acc, csub(cmul(oyd, Z[ofc]), cmul(oy, Z[otc])));
+                else if (il == ot) acc = csub(acc, csub(cmul(oyd, Z[otc]), cmul(oy, Z[ofc])));
+            }
+            return acc;
+        };
+        while (ok) {
+            for (int k = tid; k < n_halo; k += NT) Xv[R + k] = ld2(rVx, hlist[k]);
+            __syncthreads();
+            // ---------------- A: rows of this member
+            double lsum = 0.0, lmax = 0.0;
+            if (act) {
+                const double2 acc = product(Xv);
+                const double2 v = make_double2(p0.x * cs, p0.x * sn);
+                const double2 d = csub(cmulc(v, acc), sp);
+                const double rP = tk != kSlack ? d.x : 0.0;
+                const double rQ = tk == kPQ ? d.y : 0.0;
+                lsum += rP * rP + rQ * rQ;
+                lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
+                const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
+                const double2 wi = cmulc(av, v);
+                ai = cmul(av, acc);
+                Xw[tid] = wi;
+                if (!solo) rsrc_st2<true>(rW, il, wi);
+            }
+            block_reduce2<NT>(lsum, lmax, red);
+            __syncthreads();
+            block_reduce2_finish<NT>(lsum, lmax, red);
+            if (!solo) {
+                if (tid == 0) rsrc_st2<true>(rPart, mem, make_double2(lsum, lmax));
+                ok = unit_barrier(cnt, ++nbar * T, p.limit, false, progress, bar_flag);
+                if (!ok) break;
+                team_totals(lsum, lmax);
+                for (int k = tid; k < n_halo; k += NT) Xw[R + k] = rsrc_ld2<true>(rWx, hlist[k]);
+                block_reduce2<NT>(lsum, lmax, red);
+                __syncthreads();
+                block_reduce2_finish<NT>(lsum, lmax, red);
+            }
+            loss = m_res > 0.0 ? lsum / m_res : 0.0;
+            mu = isnan(lsum) ? lsum : lmax;
+            trace_mu(cold_args(), mem == 0, out_idx, it, mu);
+            const int stop = stop_status(cold_args(), loss, mu, it);
+            if (stop >= 0) {
+                stat = stop;
+                break;
+            }
+            // ---------------- B: rows of this member
+            const OptStep os = begin_update(cold_args(), sc);
+            if (act) {
+                const double2 h = product(Xw);
+                const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
+                const double gv = grad_vm(G, cs, sn, p0.x);
+                const double ga = p0.x * (G.y * cs - G.x * sn);
+                if (tk == kPQ) p0.x = opt_update(os, p0.x, gv, p1.x, p2.x);
+                if (tk != kSlack) {
+                    p0.y = opt_update(os, p0.y, ga, p1.y, p2.y);
+                    fast_sincos(p0.y, sn, cs);
+                    const double2 v = make_double2(p0.x * cs, p0.x * sn);
+                    Xv[tid] = v;
+                    if (!solo) rsrc_st2<true>(rV, il, v);
+                }
+            }
+            sched_step(cold_args(), sc, loss);
+            ++it;
+            if (mem == 0 && tid == 0 && (it & 63) == 0) atomicAdd(progress, 1);
+            if (!solo) {
+                ok = unit_barrier(cnt, ++nbar * T, p.limit, false, progress, bar_flag);
+                if (!ok) break;  // the members that arrived applied this iteration's step
+            } else {
+                __syncthreads();
+            }
+        }
+        if (act && tk != kSlack) {
+            P0[il] = p0;
+            P1[il] = p1;
+            P2[il] = p2;
+        }
+    }
+    while (ok && !compact) {
         fill([&](int x) { return ld2(rVx, x); });
         __syncthreads();
         // ---------------- A: rows of this member
@@ -546,14 +702,8 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
             if (tid == 0) rsrc_st2<true>(rPart, mem, make_double2(lsum, lmax));
             ok = unit_barrier(cnt, ++nbar * T, p.limit, false, progress, bar_flag);
             if (!ok) break;
-            // team totals: the T partials reduced in the same order by every member
-            // (their loads overlap the refill of X with w)
-            double s = 0.0, m = 0.0;
-            if (tid < T) {
-                const double2 pp = rsrc_ld2<true>(rPart, tid);
-                s = pp.x;
-                m = pp.y;
-            }
+            double s, m;
+            team_totals(s, m);
             fill([&](int x) { return rsrc_ld2<true>(rWx, x); });
             block_reduce2<NT>(s, m, red);
             __syncthreads();
@@ -635,6 +785,7 @@ __global__ __launch_bounds__(NT) void team_solve_persist_kernel(SolveArgs a, Tea
     __shared__ int bar_flag;
     __shared__ int sh_t, sh_u;
     __shared__ int scan_part[NT / kWave];
+    __shared__ int outside;
     const int tid = threadIdx.x;
     const int n_tickets = p.hdr[1];
     const int n_units = p.hdr[2];
@@ -655,7 +806,7 @@ __global__ __launch_bounds__(NT) void team_solve_persist_kernel(SolveArgs a, Tea
         const int t = __builtin_amdgcn_readfirstlane(sh_t), u = __builtin_amdgcn_readfirstlane(sh_u);
         __syncthreads();
         if (t >= n_tickets) break;
-        team_member<NT>(a, p, u, t - p.first[u], p.first[u + 1] - p.first[u], X, red, &bar_flag, scan_part);
+        team_member<NT>(a, p, u, t - p.first[u], p.first[u + 1] - p.first[u], X, red, &bar_flag, scan_part, &outside);
         __syncthreads();
     }
 }

@@ -262,3 +262,49 @@ def test_ybus_builds_from_several_threads(dpf):
     [t.start() for t in threads]
     [t.join() for t in threads]
     assert not bad
+
+
+@pytest.mark.parametrize("n,m,numbered", [(2049, 3000, False), (2500, 3900, True), (6000, 8800, True), (6000, 8800, False),
+                                          (10300, 14700, True)])
+def test_few_large_items_on_persistent_teams(dpf, n, m, numbered):
+    """Few large items on the persistent teams: members of at most one row per thread
+    with their matrix and halo in LDS (small-bandwidth numberings), members whose columns
+    lie outside their window or whose halo exceeds its list (arbitrary numberings), an
+    outage, and optimizer state in and out: follows the oracle, and two calls that
+    continue each other equal one bit for bit."""
+    rng = np.random.default_rng(48000 + n + numbered)
+    if numbered:
+        base = synth.config1(B=1, seed=48100 + n, n_bus=n, n_branch=m, n_pv=n // 6)["grid"]
+        perm = dpf.rcm_order(n, base.f, base.t, group=256)[0]
+        inv = np.empty(n, np.int64)
+        inv[perm] = np.arange(n)
+        g = synth.Grid(n, inv[base.f].astype(np.int32), inv[base.t].astype(np.int32), base.r, base.x, base.b,
+                       base.bus_type[perm], base.vm[perm], base.va[perm])
+    else:
+        g = random_grid(rng, n, m, 30)
+    B, steps = 2, 6
+    assert dpf.variants()[dpf.variant_for(n, B)]["kind"] == "wide"
+    S = oracle.injections(oracle.ybus_of(g), g.vm, g.va) * 0.98
+    vm0 = g.vm[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type == 0)
+    va0 = g.va[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type != 2)
+    nbr = synth.non_bridge_branches(n, g.f, g.t)
+    outage = np.array([-1, nbr[len(nbr) // 3]], np.int32)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+
+    def solve(parts):
+        vm, va = cu(vm0), cu(va0)
+        state, sched = torch.zeros(4, B, n, dtype=torch.float64, device="cuda"), dpf.fresh_sched_state(B, 1e-3)
+        for k in parts:
+            out = dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm, va, outage=cu(outage, torch.int32),
+                            adam_state=state, sched_state=sched, opts=dpf.Options(lr=1e-3, tol=0.0, max_iter=k))
+            assert out["iters"].tolist() == [k] * B
+        return vm, va, state, sched
+
+    vm, va, state, sched = solve([steps])
+    for c in range(B):
+        ref = oracle.solve_adam(oracle.ybus_of(g, skip=int(outage[c])), g.bus_type, S, vm0[c], va0[c],
+                                oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=steps))
+        assert np.abs(vm[c].cpu().numpy() - ref["vm"]).max() < TOL, c
+        assert np.abs(va[c].cpu().numpy() - ref["va"]).max() < TOL, c
+    for x, y in zip((vm, va, state, sched), solve([2, steps - 2])):
+        assert torch.equal(x, y)
