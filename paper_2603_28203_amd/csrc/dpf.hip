@@ -604,7 +604,7 @@ int run_split(const dpf::SolveArgs &a0, const SolveLayout &L, char *ws, const De
     p.bar = (int32_t *)(ws + L.off_bar);
     p.part = (double2 *)(ws + L.off_part);
     p.first = (const int32_t *)(ws + L.off_tfirst);
-    p.Ig = a.scratch;
+    p.Qg = (double *)a.scratch;
     p.Wg = a.scratch + 2 * a.st_stride;
     p.aborted = hdr + 7;
     p.chunk = chunk;
@@ -723,7 +723,7 @@ int run_split_device(const dpf::SolveArgs &a0, const SolveLayout &L, char *ws, c
     p.bar = (int32_t *)(ws + L.off_bar);
     p.part = (double2 *)(ws + L.off_part);
     p.first = (const int32_t *)(ws + L.off_tfirst);
-    p.Ig = a.scratch;
+    p.Qg = (double *)a.scratch;
     p.Wg = a.scratch + 2 * a.st_stride;
     p.aborted = hdr + 7;
     p.first_limit = (int64_t)(route.tail_first_wait_s * 1e9 / dev.ns_per_tick);
@@ -1629,6 +1629,7 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
         if (k.mode == dpf::kReg)
             return dpf::reg_lds_units(k.nt, n_max, std::min<int64_t>(((int64_t)n_max + 63) / 64 * 64 * wmax, L.entries),
                                       lds_units_max);
+        if (k.mode == dpf::kPair) return lds_units_max;  // one workgroup per CU in any case
         return std::max<int32_t>(2 * n_max <= lds_units_max ? 2 * n_max : n_max, 1);
     };
     a.lds_cap = lds_units(*v);

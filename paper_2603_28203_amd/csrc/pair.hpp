@@ -97,6 +97,7 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
     ItemSched sc = load_item_sched(a, out_idx);
     const double m_res = residual_count<NT>(a.bt, lo, hi, red);
     const double two_over_m = m_res > 0.0 ? 2.0 / m_res : 0.0;
+    const double half_m = 0.5 * m_res;
     const Rank2 r2 = outage_of_case(a.ov, c, lo, hi);
     if (r2.bad) return;  // reported by the call's prologue
     const int of = r2.of, ot = r2.ot;
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
 
     const int64_t cb = (int64_t)c * a.ld;
     const int64_t sb = (int64_t)c * a.s_ld;
-    double2 *__restrict__ Ig = a.scratch + cb;
+    double *__restrict__ Qg = reinterpret_cast<double *>(a.scratch) + cb;  // Im(V conj(I)) of every row (see q_lds)
     double2 *__restrict__ P0 = a.scratch + a.st_stride + cb;
     double2 *__restrict__ P1 = a.scratch + 2 * a.st_stride + cb;
     double2 *__restrict__ P2 = a.scratch + 3 * a.st_stride + cb;
@@ -114,6 +115,44 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
     const int32_t *__restrict__ scol = a.sell.col;
     const double2 *__restrict__ sval = a.sell.val;
     const int8_t *__restrict__ btp = a.bt;
+
+    // Im(V conj(I)) of the PV rows between the sweeps: in LDS behind X where it fits (one
+    // value per PV row, in row order: PV rows before each 64-row slice, then 8 B each),
+    // else in the scratch for every row
+    const int ns = (n + kWave - 1) / kWave;
+    int32_t *pv_before = reinterpret_cast<int32_t *>(X + n);
+    double *Ql = reinterpret_cast<double *>(X + n + (ns + 4) / 4);
+    bool q_lds = n + (ns + 4) / 4 <= a.lds_cap;
+    if (q_lds) {
+        for (int g = tid / kWave; g < ns; g += NT / kWave) {
+            const int il = g * kWave + lane;
+            const unsigned long long m = __ballot(il < n && btp[lo + min(il, n - 1)] == kPV);
+            if (lane == 0) pv_before[g] = __popcll(m);
+        }
+        __syncthreads();
+        if (tid < kWave) {
+            int before = 0;
+            for (int g0 = 0; g0 < ns; g0 += kWave) {
+                const int x = g0 + lane < ns ? pv_before[g0 + lane] : 0;
+                int incl = x;
+#pragma unroll
+                for (int o = 1; o < kWave; o <<= 1) {
+                    const int y = __shfl_up(incl, o, kWave);
+                    if (lane >= o) incl += y;
+                }
+                if (g0 + lane < ns) pv_before[g0 + lane] = before + incl - x;
+                before += __shfl(incl, kWave - 1, kWave);
+            }
+            if (lane == 0) pv_before[ns] = before;
+        }
+        __syncthreads();
+        q_lds = n + (ns + 4) / 4 + (pv_before[ns] + 1) / 2 <= a.lds_cap;
+    }
+    auto pv_slot = [&](int il, int8_t tk) {
+        const unsigned long long m = __ballot(tk == kPV);
+        return pv_before[il >> 6] + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                                   __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    };
 
     // the exchange vector starts as V = |V| e^{j theta}
     auto refill = [&]() {
@@ -159,13 +198,18 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                     if (il == of) acc = csub(acc, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
                     else if (il == ot) acc = csub(acc, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
                     const double2 v = X[il];
-                    const double2 d = csub(cmulc(v, acc), sp);
+                    const double2 sv = cmulc(v, acc);
+                    const double2 d = csub(sv, sp);
                     const double rP = tk != kSlack ? d.x : 0.0;
                     const double rQ = tk == kPQ ? d.y : 0.0;
                     lsum += rP * rP + rQ * rQ;
                     lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
                     const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
-                    Ig[i] = acc;
+                    if (q_lds) {
+                        if (tk == kPV) Ql[pv_slot(il, tk)] = sv.y;
+                    } else {
+                        Qg[i] = sv.y;
+                    }
                     w[j] = cmulc(av, v);
                 }
             }
@@ -201,11 +245,11 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                 const int il = s * BLK + j * NT + tid;
                 if (il < n) {
                     const int i = lo + il;
-                    // every global load of this bus first, so that they overlap the gather
+                    // loads that overlap the gather first (the moments after it: with them 5%
+                    // slower, registers being short)
                     const int8_t tk = btp[i];
-                    const double2 I = Ig[i];
                     const double2 sp = Sc[i];
-                    const double2 p0 = P0[i], p1 = P1[i], p2 = P2[i];
+                    const double2 p0 = P0[i];
                     const int gsl = __builtin_amdgcn_readfirstlane(slice0 + (il >> 6));
                     const int wdt = swidth[gsl];
                     const int base = sstart[gsl] * kWave + lane;
@@ -214,23 +258,17 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                     if (il == of) h = csub(h, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
                     else if (il == ot) h = csub(h, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
                     double vmi = p0.x, vai = p0.y;
+                    const double2 p1 = P1[i], p2 = P2[i];
                     double sn0, cs0;
                     fast_sincos(vai, sn0, cs0);
-                    const double2 v = make_double2(vmi * cs0, vmi * sn0);
-                    // the seed of the A/W sweep, rebuilt from I and the same V
-                    const double2 d = csub(cmulc(v, I), sp);
-                    const double rP = tk != kSlack ? d.x : 0.0;
-                    const double rQ = tk == kPQ ? d.y : 0.0;
-                    const double2 ai = cmul(make_double2(two_over_m * rP, two_over_m * rQ), I);
-                    const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
+                    double qv = 0.0;
+                    if (!q_lds) qv = Qg[i];
+                    else if (tk == kPV) qv = Ql[pv_slot(il, tk)];
+                    const SeedTerm g = gradient_of_row(X[il], h, vmi, cs0, sn0, sp, qv, half_m, tk == kPQ);
                     double mv = p1.x, ma = p1.y, sv = p2.x, sa = p2.y;
-                    if (tk == kPQ) {
-                        const double g = grad_vm(G, cs0, sn0, vmi);
-                        vmi = opt_update(os, vmi, g, mv, sv);
-                    }
+                    if (tk == kPQ) vmi = opt_update(os, vmi, g.vm, mv, sv);
                     if (tk != kSlack) {
-                        const double g = G.y * v.x - G.x * v.y;
-                        vai = opt_update(os, vai, g, ma, sa);
+                        vai = opt_update(os, vai, g.va, ma, sa);
                         P0[i] = make_double2(vmi, vai);
                         P1[i] = make_double2(mv, ma);
                         P2[i] = make_double2(sv, sa);

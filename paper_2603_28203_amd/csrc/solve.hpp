@@ -1067,6 +1067,26 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
     if (tid == 0) finish_item(out_idx, it, stat, mu, loss, sc);
 }
 
+// The gradient of one row from w = a conj(V) and h = (Y w), without I.  With
+// conj(G) V = conj(a) s + h V, s = V conj(I): at a PQ row the seed a holds the whole
+// residual, s = S_spec + (m/2) a; at a PV row a is real and only Im s = qv is needed,
+// 8 B kept between the sweeps where I was 16 (the paired kernel keeps it in LDS, for the
+// PV rows only).  a = w V / |V|^2.
+struct SeedTerm {
+    double vm, va;
+};
+__device__ __forceinline__ SeedTerm gradient_of_row(double2 w, double2 h, double vm, double cs, double sn, double2 sp,
+                                                    double qv, double half_m, bool pq) {
+    const double iv = 1.0 / vm;
+    const double2 e = make_double2(cs, sn);
+    double2 a = cscale(iv, cmul(w, e));
+    if (!pq) a.y = 0.0;
+    const double2 s = make_double2(sp.x + half_m * a.x, pq ? sp.y + half_m * a.y : qv);
+    const double2 t = cmulc(s, a);
+    const double2 hv = cscale(vm, cmul(h, e));
+    return SeedTerm{(t.x + hv.x) * iv, -(t.y + hv.y)};
+}
+
 // Banded variant, for sub-grids numbered with a small bandwidth: every entry of
 // the matrix has |row - col| <= NT*J in local indices (a reverse Cuthill-McKee
 // numbering gives ~80 on a 9241-bus meshed grid).  Buses are processed in blocks
@@ -1076,14 +1096,13 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
 // block by block, with one block of values held in registers instead of the
 // whole sub-grid:
 //   A/W sweep, step s: rows of block s gather V, form dS, the loss terms and
-//       w = a conj(V); I goes to scratch for the second sweep.  After a barrier
+//       w = a conj(V); Im(V conj(I)) goes to scratch for the second sweep.  After a barrier
 //       the w of block s-1 replaces V there (its readers, blocks s-2..s, are done).
 //   stop test on the reduced max|r|
 //   gradient sweep, one pass without barriers (w stays in X throughout): rows
-//       gather w, rebuild dS and a*I from I and V, form the gradient and apply
-//       the optimizer step; then X is refilled with the new V from |V| and theta.
+//       gather w, form the gradient (gradient_of_row) and apply the optimizer step; then X is refilled with the new V from |V| and theta.
 // Per bus and iteration this moves |V|, theta and the four moments once each way,
-// I (16 B written, 16 B read) and the refill's |V| and theta (16 B read); there is
+// Im(V conj(I)) (8 B written, 8 B read) and the refill's |V| and theta (16 B read); there is
 // no w round trip through memory.  (A pipelined gradient sweep that overwrote w
 // block by block with the new V moved 16 B less but, with a barrier per block,
 // ran slower: the lockstep waves stopped overlapping loads and arithmetic.)
@@ -1118,6 +1137,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
 
     const double m_res = residual_count<NT>(a.bt, lo, hi, red);
     const double two_over_m = m_res > 0.0 ? 2.0 / m_res : 0.0;
+    const double half_m = 0.5 * m_res;
 
     // N-1 outage of this case (only meaningful for a single sub-grid)
     const Rank2 r2 = outage_of_case(a.ov, c, lo, hi);
@@ -1133,7 +1153,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
     double *__restrict__ ma_c = a.st + a.st_stride + cb;
     double *__restrict__ sv_c = a.st + 2 * a.st_stride + cb;
     double *__restrict__ sa_c = a.st + 3 * a.st_stride + cb;
-    double2 *__restrict__ Ig = a.scratch + cb;  // I of the A/W sweep
+    double *__restrict__ Qg = reinterpret_cast<double *>(a.scratch) + cb;  // Im(V conj(I)) of the A/W sweep
     const double2 *__restrict__ Sc = a.s_spec + sb;
     const int32_t *__restrict__ swidth = a.sell.width;
     const int32_t *__restrict__ sstart = a.sell.start;
@@ -1187,13 +1207,14 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     if (il == of) acc = csub(acc, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
                     else if (il == ot) acc = csub(acc, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
                     const double2 v = X[il];
-                    const double2 d = csub(cmulc(v, acc), sp);
+                    const double2 sv = cmulc(v, acc);
+                    const double2 d = csub(sv, sp);
                     const double rP = tk != kSlack ? d.x : 0.0;
                     const double rQ = tk == kPQ ? d.y : 0.0;
                     lsum += rP * rP + rQ * rQ;
                     lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
                     const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
-                    Ig[i] = acc;
+                    Qg[i] = sv.y;
                     w[j] = cmulc(av, v);
                 }
             }
@@ -1232,7 +1253,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     const int i = lo + il;
                     // every global load of this bus first, so that they overlap the gather
                     const int8_t tk = btp[i];
-                    const double2 I = Ig[i];
+                    const double qv = Qg[i];
                     const double2 sp = Sc[i];
                     double vmi = vm_c[i], vai = va_c[i];
                     const double mv0 = mv_c[i], sv0 = sv_c[i], ma0 = ma_c[i], sa0 = sa_c[i];
@@ -1245,25 +1266,17 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     else if (il == ot) h = csub(h, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
                     double sn0, cs0;
                     fast_sincos(vai, sn0, cs0);
-                    const double2 v = make_double2(vmi * cs0, vmi * sn0);
-                    // the seed of the A/W sweep, rebuilt from I and the same V
-                    const double2 d = csub(cmulc(v, I), sp);
-                    const double rP = tk != kSlack ? d.x : 0.0;
-                    const double rQ = tk == kPQ ? d.y : 0.0;
-                    const double2 ai = cmul(make_double2(two_over_m * rP, two_over_m * rQ), I);
-                    const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
+                    const SeedTerm g = gradient_of_row(X[il], h, vmi, cs0, sn0, sp, qv, half_m, tk == kPQ);
                     if (tk == kPQ) {
-                        const double g = grad_vm(G, cs0, sn0, vmi);
                         double mv = mv0, sv = sv0;
-                        vmi = opt_update(os, vmi, g, mv, sv);
+                        vmi = opt_update(os, vmi, g.vm, mv, sv);
                         vm_c[i] = vmi;
                         mv_c[i] = mv;
                         sv_c[i] = sv;
                     }
                     if (tk != kSlack) {
-                        const double g = G.y * v.x - G.x * v.y;
                         double ma = ma0, sa = sa0;
-                        vai = opt_update(os, vai, g, ma, sa);
+                        vai = opt_update(os, vai, g.va, ma, sa);
                         va_c[i] = vai;
                         ma_c[i] = ma;
                         sa_c[i] = sa;

@@ -68,7 +68,7 @@ struct SplitArgs {
     int64_t slice;        // wall-clock ticks per launch, 0 = no limit
     int32_t *bar;         // [n_list][kBarStride] arrival counters (first word of each), zero at launch
     double2 *part;        // [first[n_list]] member partials (loss sum, max|r|), team k at first[k]
-    double2 *Ig;          // [B][ld] I of the A sweep
+    double *Qg;           // [B][ld] Im(V conj(I)) of the A sweep
     double2 *Wg;          // [B][ld] exchanged w
     int32_t *aborted;     // set when a team abandoned a barrier
     int64_t first_limit;  // wall-clock ticks a member waits at the first barrier
@@ -143,6 +143,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
     ItemSched sc = load_item_sched(a, c);
     const double m_res = residual_count<NT>(a.bt, 0, n, red);
     const double two_over_m = m_res > 0.0 ? 2.0 / m_res : 0.0;
+    const double half_m = 0.5 * m_res;
     const Rank2 r2 = outage_of_case(a.ov, c, 0, n);
     if (r2.bad) return;  // reported by the call's prologue (status stays DPF_BAD_OUTAGE); every member leaves
     const int of = r2.of, ot = r2.ot;
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
     double *__restrict__ ma_c = a.st + a.st_stride + cb;
     double *__restrict__ sv_c = a.st + 2 * a.st_stride + cb;
     double *__restrict__ sa_c = a.st + 3 * a.st_stride + cb;
-    double2 *__restrict__ Ig = p.Ig + cb;
+    double *__restrict__ Qg = p.Qg + cb;
     double2 *__restrict__ Wg = p.Wg + cb;
     const double2 *__restrict__ Sc = a.s_spec + (int64_t)c * a.s_ld;
     const int32_t *__restrict__ swidth = a.sell.width;
@@ -299,12 +300,13 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
             if (il == of) acc = csub(acc, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
             else if (il == ot) acc = csub(acc, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
             const double2 v = X[il];
-            const double2 d = csub(cmulc(v, acc), sp);
+            const double2 sv = cmulc(v, acc);
+            const double2 d = csub(sv, sp);
             const double rP = tk != kSlack ? d.x : 0.0;
             const double rQ = tk == kPQ ? d.y : 0.0;
             lsum += rP * rP + rQ * rQ;
             lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
-            Ig[il] = acc;
+            Qg[il] = sv.y;
             const double2 w = cmulc(make_double2(two_over_m * rP, two_over_m * rQ), v);
             if (solo) Wg[il] = w;
             else st_dev2(Wg + il, w);
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
         const OptStep os = begin_update(cold_args(), sc);
         for (int il = rlo + tid; il < rhi; il += NT) {
             const int8_t tk = btp[il];
-            const double2 I = Ig[il];
+            const double qv = Qg[il];
             const double2 sp = Sc[il];
             double vmi = vm_c[il], vai = va_c[il];
             const double mv0 = mv_c[il], sv0 = sv_c[il], ma0 = ma_c[il], sa0 = sa_c[il];
@@ -383,24 +385,17 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
             else if (il == ot) h = csub(h, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
             double sn0, cs0;
             fast_sincos(vai, sn0, cs0);
-            const double2 v = make_double2(vmi * cs0, vmi * sn0);
-            const double2 d = csub(cmulc(v, I), sp);
-            const double rP = tk != kSlack ? d.x : 0.0;
-            const double rQ = tk == kPQ ? d.y : 0.0;
-            const double2 ai = cmul(make_double2(two_over_m * rP, two_over_m * rQ), I);
-            const double2 G = make_double2(ai.x + h.x, ai.y - h.y);
+            const SeedTerm g = gradient_of_row(X[il], h, vmi, cs0, sn0, sp, qv, half_m, tk == kPQ);
             if (tk == kPQ) {
-                const double g = grad_vm(G, cs0, sn0, vmi);
                 double mv = mv0, sv = sv0;
-                vmi = opt_update(os, vmi, g, mv, sv);
+                vmi = opt_update(os, vmi, g.vm, mv, sv);
                 st(vm_c + il, vmi);
                 mv_c[il] = mv;
                 sv_c[il] = sv;
             }
             if (tk != kSlack) {
-                const double g = G.y * v.x - G.x * v.y;
                 double ma = ma0, sa = sa0;
-                vai = opt_update(os, vai, g, ma, sa);
+                vai = opt_update(os, vai, g.va, ma, sa);
                 st(va_c + il, vai);
                 ma_c[il] = ma;
                 sa_c[il] = sa;

@@ -308,3 +308,39 @@ def test_few_large_items_on_persistent_teams(dpf, n, m, numbered):
         assert np.abs(va[c].cpu().numpy() - ref["va"]).max() < TOL, c
     for x, y in zip((vm, va, state, sched), solve([2, steps - 2])):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n,n_pv", [(10208, 300), (10100, 1700), (9300, 3700), (4097, 0)])
+def test_paired_kernel_with_and_without_room_for_pv_values(dpf, n, n_pv):
+    """The paired-state kernel keeps one value per PV row in LDS where it fits behind the
+    exchange vector (the largest sub-grid and many PV rows leave no room: the scratch
+    takes them): equal to the banded kernel bit for bit, and follows the oracle."""
+    rng = np.random.default_rng(49000 + n)
+    k = np.arange(1, n)
+    f = np.concatenate([k - 1 - rng.integers(0, np.minimum(k, 60)), k[:n // 2]])
+    t = np.concatenate([k, np.minimum(k[:n // 2] + rng.integers(2, 80, n // 2), n - 1)])
+    f, t = f[f != t].astype(np.int32), t[f != t].astype(np.int32)
+    nb = len(f)
+    bt = np.zeros(n, np.int8)
+    kinds = rng.permutation(n)
+    bt[kinds[0]] = 2
+    bt[kinds[1:1 + n_pv]] = 1
+    va = rng.uniform(-0.1, 0.1, n)
+    va[kinds[0]] = 0.0
+    g = synth.Grid(n, f, t, rng.uniform(0.01, 0.1, nb), rng.uniform(0.05, 0.3, nb), rng.uniform(0, 0.05, nb), bt,
+                   rng.uniform(0.97, 1.03, n), va)
+    S = oracle.injections(oracle.ybus_of(g), g.vm, g.va) * 0.98
+    vm0, va0 = g.vm[None] * np.ones((3, 1)), g.va[None] + rng.normal(0, 1e-2, (3, n)) * (bt != 2)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    got = {}
+    for kind in ("banded-stream", "banded-pair"):
+        index = next(v["index"] for v in dpf.variants() if v["kind"] == kind and v["buses_per_thread"] == 4)
+        vm, va_ = cu(vm0), cu(va0)
+        dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm, va_, route=dpf.Route(variant=index),
+                  opts=dpf.Options(lr=1e-3, tol=0.0, max_iter=5))
+        got[kind] = vm, va_
+    assert all(torch.equal(a, b) for a, b in zip(got["banded-stream"], got["banded-pair"]))
+    ref = oracle.solve_adam(oracle.ybus_of(g), g.bus_type, S, vm0[1], va0[1],
+                            oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=5))
+    assert np.abs(got["banded-pair"][0][1].cpu().numpy() - ref["vm"]).max() < TOL
+    assert np.abs(got["banded-pair"][1][1].cpu().numpy() - ref["va"]).max() < TOL
