@@ -140,10 +140,13 @@ def _ptr(t):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle (torch.cuda.current_stream() builds a Stream object: 5 us)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _dev(t, dtype, device):
+    if isinstance(t, torch.Tensor) and t.dtype == dtype and t.device == device and t.is_contiguous():
+        return t  # nothing to convert (three dispatched calls less)
     t = torch.as_tensor(t)
     return t.to(device=device, dtype=dtype).contiguous()
 
@@ -502,8 +505,7 @@ class DPFLoss(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, vm, va, grid, bus_type, s_spec, outage=None):
-        r = mismatch_grad(grid, bus_type, s_spec, vm.detach(), va.detach(), outage=outage, want_dS=False,
-                          want_grad=True)
+        r = mismatch_grad(grid, bus_type, s_spec, vm, va, outage=outage, want_dS=False, want_grad=True)
         ctx.save_for_backward(r["g_vm"], r["g_va"])
         ctx.mark_non_differentiable(r["max_mis"])
         return r["loss"], r["max_mis"]
@@ -511,7 +513,8 @@ class DPFLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_loss, grad_mx):
         gv, ga = ctx.saved_tensors
-        return grad_loss[:, None] * gv, grad_loss[:, None] * ga, None, None, None, None
+        scale = grad_loss.unsqueeze(1)
+        return scale * gv, scale * ga, None, None, None, None
 
 
 # ---------------------------------------------------------------- autotuner

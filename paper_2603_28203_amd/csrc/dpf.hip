@@ -924,7 +924,8 @@ int run_eval_by_case(const dpf::EvalArgs &a, int32_t B, bool both, hipStream_t s
     const EvalFn fn = both ? s->two : s->one;
     if (!fn) return fail(DPF_EHIP, "no evaluation kernel of this size");
     const size_t lds = (size_t)a.n * 16 * (both ? 2 : 1);
-    DPF_HIP(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (lds > 32 * 1024)  // within every launch's default limit otherwise
+        DPF_HIP(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(fn, dim3(B), dim3(s->nt), lds, st, a);
     DPF_HIP(hipGetLastError());
     return DPF_OK;
