@@ -265,7 +265,8 @@ int dpf_param_grad(const dpf_grid_t *g, int32_t B, int32_t ld, const int8_t *bus
  *                    iteration counts, optimizer and schedule state carry over,
  *                    so results equal a call without handoff up to the rounding
  *                    of the other path.  Applies to the streaming and banded
- *                    kernels; a call of at most this many items is
+ *                    kernels (by default a call with a handoff above 2048 buses
+ *                    runs the streaming one); a call of at most this many items is
  *                    handed over after its first 32 iterations.  0 (default) = off
  *   tail_team      : how handed-over items finish.  0 (default): on the
  *                    multi-workgroup path.  > 0 (at most 1024): on the split
@@ -551,7 +552,9 @@ int32_t dpf_solve_max_sub_buses(void);
  * and is guarded by a mutex.
  *   dpf_solve_variant_count : number of variants
  *   dpf_solve_variant_info  : threads per workgroup, buses per thread (0 = any),
- *                             and the kind: register-resident (0), streaming (1),
+ *                             and the kind: register-resident (0; by default up
+ *                             to 2048 buses, up to 4096 in calls of a single grid
+ *                             without a handoff), streaming (1),
  *                             banded with a barrier-free gradient sweep (2),
  *                             multi-workgroup (3: not a kernel of its own --
  *                             every sub-grid of the call is spread over many

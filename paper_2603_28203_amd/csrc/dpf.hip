@@ -199,8 +199,9 @@ Variant make_pair_variant() {
 
 
 // Register-resident variants up to 4096 buses per item (the last two entries above
-// 2048), the 1024-thread streaming variant above (any size).  The banded variants (k = buses per thread per block)
-// serve sub-grids whose bandwidth is at most threads * k; the others go to the
+// 2048; at the end, so that the indices callers have stored keep their meaning), the
+// 1024-thread streaming variant above (any size).  The banded variants (k = buses per
+// thread per block) serve sub-grids whose bandwidth is at most threads * k; the others go to the
 // default variant of the size in the same call.  The kWide entry is not a
 // workgroup-per-item kernel: it sends every sub-grid of the call to the
 // multi-workgroup path, which spreads one item over many CUs.  Kinds measured and
@@ -237,12 +238,13 @@ int items_bucket(int64_t items) { return items <= 64 ? 0 : (items <= 256 ? 1 : 2
 // Items larger than this (buses) that fill at most half of the chip (2 items <= CUs)
 // are solved faster spread over several workgroups than one workgroup each (measured
 // on the persistent teams: 9241 buses, 64 cases, 38 against 68 us per iteration; 1354
-// buses: one workgroup wins; 256 cases of 3000 buses, one per CU: the per-item
-// streaming kernel, 29 against 39 us).
+// buses: one workgroup wins; 3000 buses: 64 cases 9.5 us on teams against 14.6 on the
+// resident kernel, 256 cases, one per CU, 39 against 14.6).
 constexpr int32_t kWideDefaultBuses = 2048;
 
-// first register-resident variant that holds n_max buses, else the streaming one.
-// small_only: no register-resident variant above 2048 buses, for calls that may hand
+// first register-resident variant that holds n_max buses, else the streaming one
+// (256 cases, us per iteration on the resident kernels against streaming: 2500 buses
+// 14.2 / 20, 4000 22.7 / 30.7).  small_only: no register-resident variant above 2048 buses, for calls that may hand
 // their items over (those kernels cannot) and calls of several sub-grids (their threads
 // carry 6 or 8 rows also for an item of a few)
 int default_variant_index(int32_t n_max, bool small_only = false) {
@@ -370,7 +372,7 @@ static SolveLayout solve_layout(const dpf_grid_t *g, int32_t n_sub, const int32_
     if (streaming) {
         L.off_mom = o;  // Adam moments [4][B][ld] when the caller passes none
         o += align_up(sizeof(double) * 4 * (size_t)B * ld, 256);
-        L.off_scr = o;  // V, a*I and w [3][B][ld] complex (paired state: I and the three pairs, [4][B][ld];
+        L.off_scr = o;  // V, a*I and w [3][B][ld] complex (paired state: Im(V conj(I)) and the three pairs, [4][B][ld];
                         // persistent teams: a*I, V, w and the three pairs, [6][B][ld])
         o += align_up(sizeof(double2) * (teams ? 6 : pairs ? 4 : 3) * (size_t)B * ld, 256);
     }

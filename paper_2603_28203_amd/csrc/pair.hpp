@@ -6,14 +6,17 @@
 // iterates equal the banded kernel's bit for bit.
 //
 // Why: the banded kernel on gfx950 is bound by the vector-memory instructions
-// its waves issue per bus and the bytes they move (rocprofv3: about 37 memory
-// instructions per bus-iteration, 160 bytes to and from HBM against the 96-byte
-// floor).  Here a bus's state takes three 16-byte loads and three 16-byte stores
-// per iteration instead of six 8-byte ones each way, and the refill of the
-// exchange vector one load instead of two; the bytes are the same (5% less time
-// per iteration on the N-1 batch).  Removing VALU work instead (one sincos per
-// bus-iteration, Adam's bias corrections as per-iteration scalars) at the price
-// of one more 16-byte store per bus was measured 3% slower.
+// its waves issue per bus and the bytes they move.  Here a bus's state takes three
+// 16-byte loads and three 16-byte stores per iteration instead of six 8-byte ones
+// each way, and the refill of the exchange vector one load instead of two (5% less
+// time per iteration on the N-1 batch).  Between the sweeps only Im(V conj(I)) of the
+// PV rows is kept, in LDS behind the exchange vector where it fits, so that a
+// bus-iteration moves the 96 bytes of state plus the refill's 16.  100 iterations of
+// 1024 cases of 9241 buses: 16.7 ms with I kept in memory, the bias corrections and
+// divisions per bus and 10 spilled registers; 15.8 with the divisions shared, 15.65
+// without the spills, 14.5 now.  Timing-only copies: 14.4 without the kept value at
+// all, 13.8 without the refill.  Slower: joint gathers or other group sizes (3-5%),
+// the kept value in memory for the PV rows only (partial sectors, 6%).
 // pair_in_kernel fills the pairs from the caller's arrays before the solve and
 // pair_out_kernel writes them back after it (also for items paused for the tail
 // handoff, whose state the split kernel reads from the caller's layout).
@@ -67,7 +70,8 @@ __global__ void pair_out_kernel(int32_t n, int64_t ld, int32_t B, double *__rest
     }
 }
 
-// a.scratch holds [4][B][ld] complex: I of the A/W sweep, then P0, P1, P2
+// a.scratch holds [4][B][ld] complex: the first array is Im(V conj(I)) between the sweeps
+// (doubles, used where LDS has no room for it), then P0, P1, P2
 template <int NT, int J>
 __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
     constexpr int BLK = NT * J;

@@ -12,18 +12,21 @@
 // Per iteration, for every bus i owned by the thread (i = lo + tid + k*NT):
 //   A: I_i = sum_j Y_ij X_j (X = V) [- outage block];  dS_i = V_i conj(I_i) - S_i
 //      r^P = [PV|PQ] Re dS, r^Q = [PQ] Im dS; loss and max|r| (workgroup reduce)
-//      a_i = (2/m)(r^P + j r^Q); w_i = a_i conj(V_i); keep a_i I_i
+//      a_i = (2/m)(r^P + j r^Q); w_i = a_i conj(V_i); keep a_i I_i (the banded kernels
+//      only Im(V_i conj(I_i)), see gradient_of_row)
 //   stop test on max|r| (before the update, as the loop's convergence check)
 //   B: h_i = sum_j Y_ij X_j (X = w; Y^T = Y) [- outage block]
 //      G_i = a_i I_i + conj(h_i); g_vm = Re(conj(G) V)/vm at PQ; g_va = Im(G conj V)
 //      Adam on the learnable entries; V_i = vm e^{j va}
-// Two storage modes:
-//   kReg    : the item's state (vm, va, Adam moments, S_spec, V, aI) stays in
-//             registers for the whole solve (small sub-grids, K <= 2).
-//   kGlobal : state in global memory (the caller's vm/va/adam arrays, scratch
-//             for V and a*I), streamed once per iteration (large sub-grids).
-// LDS is double-buffered (separate V and w arrays, 2 barriers per iteration)
-// when 2n complex values fit, single-buffered (4 barriers) otherwise.
+// Where the state (vm, va, the moments) lives between iterations:
+//   kReg        : in registers; up to 2048 buses with the matrix in LDS where it fits
+//                 (team_solve_reg_kernel), 2049 to 4096 with the matrix read from L2
+//                 (team_solve_resident_kernel)
+//   kGlobal     : in the caller's arrays, streamed once per iteration (any size)
+//   kBandStream : the same, with w in place over V in LDS (small bandwidths)
+//   kPair       : as kBandStream, the state as three 16-byte pairs (pair.hpp)
+// The register and resident kernels keep V and w in two LDS arrays (2 barriers per
+// iteration); the others exchange through one.
 #pragma once
 
 #include "../../include/dpf.h"
@@ -36,7 +39,7 @@
 namespace dpf {
 
 enum StoreMode {
-    kReg = 0,         // state in registers
+    kReg = 0,         // state in registers (register and resident kernels)
     kGlobal = 1,      // streaming: state in global memory
     kBandStream = 2,  // banded, barrier-free gradient sweep
     kWide = 3,        // the multi-workgroup path for a whole call

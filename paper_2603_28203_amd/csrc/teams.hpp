@@ -14,7 +14,9 @@
 // always assembles when T workgroups fit on the device (T is capped at 32 and at
 // half of the launch).
 //
-// A member owns rows [rlo, rhi) of its sub-grid (whole 64-row slices) and keeps in
+// A member owns rows [rlo, rhi) of its sub-grid (whole 64-row slices).  One of at most
+// one row per thread keeps state, matrix and halo on chip where they fit (the compact
+// form, in the kernel); any other follows the general form described here: it keeps in
 // LDS a window of the exchanged vector: its rows plus the sub-grid's bandwidth on
 // each side as far as the LDS holds (the whole sub-grid when it fits).  An entry
 // outside the window (a bandwidth wider than the LDS allows, or the two buses of
@@ -67,14 +69,14 @@
 
 namespace dpf {
 
-// 1024 threads (16 waves, one workgroup per CU): ~30 VGPRs spill at the 128-register
-// limit, yet an iteration runs 1.2-1.5x faster than at 512 threads without spills
-// (measured on 64 cases of 9241 buses, 256 cases of 3000 and the uneven batch).
-// The gathers unroll by 2 (by 4: 44 spilled registers and 5-10% slower).
+// 1024 threads (16 waves, one workgroup per CU): some VGPRs spill at the 128-register
+// limit, yet an iteration of the general form runs 1.2-1.5x faster than at 512 threads
+// without spills (measured on 64 cases of 9241 buses, 256 cases of 3000 and the uneven
+// batch).
 constexpr int kTeamThreads = 1024;
 constexpr int kPlanThreads = 512;
-// members per team at most: one 9241-bus case takes 14 us per iteration on 32
-// members, 19 us on 128 (more arrivals per barrier, more halo per row)
+// members per team at most: in the general form one 9241-bus case took 14 us per
+// iteration on 32 members, 19 us on 128 (more arrivals per barrier, more halo per row)
 constexpr int kTeamMaxMembers = 32;
 constexpr int kLoadKeys = 32;      // half-octave buckets of the per-member load
 constexpr int kTeamMaxWaves = 8;
