@@ -284,8 +284,10 @@ struct EvalArgs {
 // gradients), then the adjoint rows.  With conj(G) V = conj(a) V conj(I) + h V the
 // gradient needs no a*I: a row keeps conj(a) (dS + S) instead of I.
 // One launch instead of five and no V, w and a*I through memory (per bus and case 168 B
-// before, 64 to 80 B here).  Large grids are bound by the matrix reads: a wave's 16-byte
-// loads of 64 CSR rows touch about 36 cache lines each.  Device time of a call on an
+// before, 64 to 80 B here).  Bound by the chain of matrix load and LDS gather of every
+// row: four lanes sharing a row, 16 rows per load and so a quarter of the cache lines
+// per load, is 4 to 20% slower (1354 x 64 13.1 -> 15.7 us, 9241 x 256 81 -> 97), its
+// gathers and sums being more.  Device time of a call on an
 // MI355X, five launches -> this: 118 buses x 8 cases 14 -> 6 us, 1354 x 64 22.5 -> 13.3
 // (with branch gradients 21.2 -> 10.6), 5000 x 256 120 -> 43, 9241 x 256 241 -> 79.
 template <int NT, int K, bool BOTH>

@@ -202,17 +202,17 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                     if (il == of) acc = csub(acc, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
                     else if (il == ot) acc = csub(acc, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
                     const double2 v = X[il];
-                    const double2 sv = cmulc(v, acc);
-                    const double2 d = csub(sv, sp);
+                    const double2 d = residual_of_row(v, acc, sp);
+                    const double qv = fma(v.y, acc.x, -(v.x * acc.y));
                     const double rP = tk != kSlack ? d.x : 0.0;
                     const double rQ = tk == kPQ ? d.y : 0.0;
                     lsum += rP * rP + rQ * rQ;
                     lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
                     const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
                     if (q_lds) {
-                        if (tk == kPV) Ql[pv_slot(il, tk)] = sv.y;
+                        if (tk == kPV) Ql[pv_slot(il, tk)] = qv;
                     } else {
-                        Qg[i] = sv.y;
+                        Qg[i] = qv;
                     }
                     w[j] = cmulc(av, v);
                 }

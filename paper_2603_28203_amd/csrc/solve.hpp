@@ -1070,6 +1070,15 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
     if (tid == 0) finish_item(out_idx, it, stat, mu, loss, sc);
 }
 
+// V conj(I) - S with S inside the chain of multiply-adds: its rounding then differs from
+// that of any S formed as a product before.  A start at such an S (an outage from the
+// base case's own injections) would otherwise leave residuals of exactly zero at most
+// buses, which Adam turns into a longer path: 264 instead of 50 steps at the median to
+// max|r| < 1e-3 on 1024 outages of 9241 buses, 4% more steps to 1e-6.
+__device__ __forceinline__ double2 residual_of_row(double2 v, double2 i, double2 s) {
+    return make_double2(fma(v.x, i.x, fma(v.y, i.y, -s.x)), fma(v.y, i.x, fma(-v.x, i.y, -s.y)));
+}
+
 // The gradient of one row from w = a conj(V) and h = (Y w), without I.  With
 // conj(G) V = conj(a) s + h V, s = V conj(I): at a PQ row the seed a holds the whole
 // residual, s = S_spec + (m/2) a; at a PV row a is real and only Im s = qv is needed,
@@ -1210,14 +1219,14 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     if (il == of) acc = csub(acc, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
                     else if (il == ot) acc = csub(acc, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
                     const double2 v = X[il];
-                    const double2 sv = cmulc(v, acc);
-                    const double2 d = csub(sv, sp);
+                    const double2 d = residual_of_row(v, acc, sp);
+                    const double qv = fma(v.y, acc.x, -(v.x * acc.y));
                     const double rP = tk != kSlack ? d.x : 0.0;
                     const double rQ = tk == kPQ ? d.y : 0.0;
                     lsum += rP * rP + rQ * rQ;
                     lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
                     const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
-                    Qg[i] = sv.y;
+                    Qg[i] = qv;
                     w[j] = cmulc(av, v);
                 }
             }

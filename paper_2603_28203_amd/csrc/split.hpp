@@ -300,13 +300,13 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
             if (il == of) acc = csub(acc, csub(cmul(oyd, X[of]), cmul(oy, X[ot])));
             else if (il == ot) acc = csub(acc, csub(cmul(oyd, X[ot]), cmul(oy, X[of])));
             const double2 v = X[il];
-            const double2 sv = cmulc(v, acc);
-            const double2 d = csub(sv, sp);
+            const double2 d = residual_of_row(v, acc, sp);
+            const double qv = fma(v.y, acc.x, -(v.x * acc.y));
             const double rP = tk != kSlack ? d.x : 0.0;
             const double rQ = tk == kPQ ? d.y : 0.0;
             lsum += rP * rP + rQ * rQ;
             lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
-            Qg[il] = sv.y;
+            Qg[il] = qv;
             const double2 w = cmulc(make_double2(two_over_m * rP, two_over_m * rQ), v);
             if (solo) Wg[il] = w;
             else st_dev2(Wg + il, w);
