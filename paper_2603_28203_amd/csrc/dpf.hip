@@ -797,13 +797,13 @@ int run_teams(const dpf::SolveArgs &a0, const SolveLayout &L, char *ws, int32_t 
     // the state as pairs for the launch, and back to the caller's arrays after it
     // (every entry, unfinished items included)
     const dim3 pgrid((unsigned)((a.n_bus + 255) / 256), (unsigned)std::min<int32_t>(B, 65535));
-    hipLaunchKernelGGL(dpf::pair_in_kernel, pgrid, dim3(256), 0, st, a.n_bus, a.ld, B, a.vm, a.va, a.st,
-                       a.st_stride, a.st_fresh, p.P0, p.P1, p.P2);
+    hipLaunchKernelGGL(dpf::pair_in_kernel, pgrid, dim3(256), 0, st, a.n_bus, a.ld, B, dpf::PairSkip{}, a.vm,
+                       a.va, a.st, a.st_stride, a.st_fresh, p.P0, p.P1, p.P2);
     hipLaunchKernelGGL(dpf::team_plan_kernel, dim3(1), dim3(dpf::kPlanThreads), 0, st, n_sub, a.sub_off, a.n_bus,
                        a.sub_bw, B, p);
     hipLaunchKernelGGL(fn, dim3(grid), dim3(dpf::kTeamThreads), (size_t)lds, st, a, p);
-    hipLaunchKernelGGL(dpf::pair_out_kernel, pgrid, dim3(256), 0, st, a.n_bus, a.ld, B, a.vm, a.va, a.st,
-                       a.st_stride, p.P0, p.P1, p.P2);
+    hipLaunchKernelGGL(dpf::pair_out_kernel, pgrid, dim3(256), 0, st, a.n_bus, a.ld, B, dpf::PairSkip{}, a.vm,
+                       a.va, a.st, a.st_stride, p.P0, p.P1, p.P2);
     DPF_HIP(hipGetLastError());
     return DPF_OK;
 }
@@ -1710,18 +1710,19 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
     if (has_small) {
         const dim3 pgrid((g->n_bus + 255) / 256, std::min<int32_t>(B, 65535));
         double2 *P = a.scratch + a.st_stride;  // the pairs follow I in the scratch
+        const dpf::PairSkip skip{has_wide ? sub_offset_dev : nullptr, n_sub, cap};
         if (pairs)
-            hipLaunchKernelGGL(dpf::pair_in_kernel, pgrid, dim3(256), 0, st, g->n_bus, (int64_t)ld, B, vm, va, a.st,
-                               a.st_stride, a.st_fresh, P, P + a.st_stride, P + 2 * a.st_stride);
+            hipLaunchKernelGGL(dpf::pair_in_kernel, pgrid, dim3(256), 0, st, g->n_bus, (int64_t)ld, B, skip, vm, va,
+                               a.st, a.st_stride, a.st_fresh, P, P + a.st_stride, P + 2 * a.st_stride);
         DPF_HIP(hipFuncSetAttribute((const void *)v->fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds_bytes));
         hipLaunchKernelGGL(v->fn, dim3(items), dim3(v->nt), lds_bytes, st, a);
         DPF_HIP(hipGetLastError());
-        // the pairs back to the caller's layout (every item, paused ones included) before
-        // any other path reads the state
+        // the pairs back to the caller's layout (every item of this path, paused ones
+        // included) before any other path reads the state
         if (pairs)
-            hipLaunchKernelGGL(dpf::pair_out_kernel, pgrid, dim3(256), 0, st, g->n_bus, (int64_t)ld, B, vm, va, a.st,
-                               a.st_stride, P, P + a.st_stride, P + 2 * a.st_stride);
+            hipLaunchKernelGGL(dpf::pair_out_kernel, pgrid, dim3(256), 0, st, g->n_bus, (int64_t)ld, B, skip, vm, va,
+                               a.st, a.st_stride, P, P + a.st_stride, P + 2 * a.st_stride);
         DPF_HIP(hipGetLastError());
         if (dpf::is_banded(v->mode)) {
             // items whose bandwidth exceeds the banded block go to the general variant

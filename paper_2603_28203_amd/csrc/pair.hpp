@@ -30,14 +30,27 @@
 
 namespace dpf {
 
+// Rows the pairs leave alone: those of sub-grids above the cap, which the
+// multi-workgroup path runs at the same time on another stream, its vectors in the
+// same scratch arrays.  sub_off null: no such sub-grid in the call.
+struct PairSkip {
+    const int32_t *sub_off;
+    int32_t n_sub, cap;
+    __device__ __forceinline__ bool operator()(int32_t i) const {
+        if (!sub_off) return false;
+        const int32_t s = find_sub(i, n_sub, sub_off);
+        return sub_off[s + 1] - sub_off[s] > cap;
+    }
+};
+
 // P0..P2 [B][ld] complex from vm, va and the moments st [4][B][ld] (m_vm, m_va,
 // s_vm, s_va); fresh: the moments start at zero
-__global__ void pair_in_kernel(int32_t n, int64_t ld, int32_t B, const double *__restrict__ vm,
+__global__ void pair_in_kernel(int32_t n, int64_t ld, int32_t B, PairSkip skip, const double *__restrict__ vm,
                                const double *__restrict__ va, const double *__restrict__ st, int64_t stride,
                                int32_t fresh, double2 *__restrict__ P0, double2 *__restrict__ P1,
                                double2 *__restrict__ P2) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || skip(i)) return;
     for (int32_t c = blockIdx.y; c < B; c += gridDim.y) {  // the grid's y extent may be below B
         const int64_t o = (int64_t)c * ld + i;
         P0[o] = make_double2(vm[o], va[o]);
@@ -51,13 +64,14 @@ __global__ void pair_in_kernel(int32_t n, int64_t ld, int32_t B, const double *_
     }
 }
 
-// the pairs back to vm, va and the moments (every entry: the kernel leaves the
-// fixed coordinates as they came in)
-__global__ void pair_out_kernel(int32_t n, int64_t ld, int32_t B, double *__restrict__ vm, double *__restrict__ va,
-                                double *__restrict__ st, int64_t stride, const double2 *__restrict__ P0,
-                                const double2 *__restrict__ P1, const double2 *__restrict__ P2) {
+// the pairs back to vm, va and the moments (every entry of those rows: the kernel
+// leaves the fixed coordinates as they came in)
+__global__ void pair_out_kernel(int32_t n, int64_t ld, int32_t B, PairSkip skip, double *__restrict__ vm,
+                                double *__restrict__ va, double *__restrict__ st, int64_t stride,
+                                const double2 *__restrict__ P0, const double2 *__restrict__ P1,
+                                const double2 *__restrict__ P2) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || skip(i)) return;
     for (int32_t c = blockIdx.y; c < B; c += gridDim.y) {
         const int64_t o = (int64_t)c * ld + i;
         const double2 p0 = P0[o], p1 = P1[o], p2 = P2[o];

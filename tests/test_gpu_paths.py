@@ -344,3 +344,49 @@ def test_paired_kernel_with_and_without_room_for_pv_values(dpf, n, n_pv):
                             oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=5))
     assert np.abs(got["banded-pair"][0][1].cpu().numpy() - ref["vm"]).max() < TOL
     assert np.abs(got["banded-pair"][1][1].cpu().numpy() - ref["va"]).max() < TOL
+
+
+def collection(grids):
+    """Grids side by side as the sub-grids of one call: (offsets, branch arrays, bus kinds)."""
+    off = np.cumsum([0] + [g.n_bus for g in grids])
+    f, t = (np.concatenate([getattr(g, k) + o for g, o in zip(grids, off)]) for k in "ft")
+    r, x, b, bt = (np.concatenate([getattr(g, k) for g in grids]) for k in ("r", "x", "b", "bus_type"))
+    return off.tolist(), (f, t, r, x, b), bt
+
+
+def check_mixed_call(dpf, seed, grids, B, steps, team_cap, kind, J):
+    """Every item of a call whose sub-grids above ``team_cap`` run on the host-driven
+    multi-workgroup path beside a named banded kernel follows the oracle."""
+    rng = np.random.default_rng(seed)
+    off, branches, bt = collection(grids)
+    n = off[-1]
+    S = np.concatenate([oracle.injections(oracle.ybus_of(g), g.vm, g.va) for g in grids]) * 0.98
+    vm0 = np.concatenate([g.vm for g in grids])[None] + rng.normal(0, 1e-2, (B, n)) * (bt == 0)
+    va0 = np.concatenate([g.va for g in grids])[None] + rng.normal(0, 1e-2, (B, n)) * (bt != 2)
+    index = next(v["index"] for v in dpf.variants() if v["kind"] == kind and v["buses_per_thread"] == J)
+    vm, va = cu(vm0), cu(va0)
+    state = torch.zeros(4, B, n, dtype=torch.float64, device="cuda")
+    Yg = dpf.build_ybus(n, *branches)
+    out = dpf.solve(Yg, bt, cu(S, torch.complex128), vm, va, sub_offset=off, adam_state=state,
+                    opts=dpf.Options(lr=1e-3, tol=0.0, max_iter=steps),
+                    route=dpf.Route(variant=index, team_cap=team_cap, wide_host=1))
+    assert out["iters"].flatten().tolist() == [steps] * (B * len(grids))
+    for k, g in enumerate(grids):
+        sl = slice(off[k], off[k + 1])
+        for c in sorted({0, B - 1}):
+            ref = oracle.solve_adam(oracle.ybus_of(g), g.bus_type, S[sl], vm0[c, sl], va0[c, sl],
+                                    oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=steps))
+            assert np.abs(vm[c, sl].cpu().numpy() - ref["vm"]).max() < TOL, (k, c)
+            assert np.abs(va[c, sl].cpu().numpy() - ref["va"]).max() < TOL, (k, c)
+    # every learnable coordinate of every item left its moments
+    assert (state[0][:, cu(bt == 0, torch.bool)] != 0).all() and (state[1][:, cu(bt != 2, torch.bool)] != 0).all()
+
+
+@pytest.mark.parametrize("J", [2, 4])
+def test_paired_kernel_beside_the_multi_workgroup_path(dpf, J):
+    """The paired kernel's state pairs belong to its own items: the larger sub-grids that
+    the multi-workgroup path solves at the same time keep their scratch and their
+    results, whichever of the two ends first."""
+    rng = np.random.default_rng(50000 + J)
+    grids = [random_grid(rng, n, int(1.5 * n)) for n in (900, 400, 700, 60, 300)]
+    check_mixed_call(dpf, 50010 + J, grids, 3, 40, 500, "banded-pair", J)
