@@ -606,7 +606,7 @@ int run_split(const dpf::SolveArgs &a0, const SolveLayout &L, char *ws, const De
     p.bar = (int32_t *)(ws + L.off_bar);
     p.part = (double2 *)(ws + L.off_part);
     p.first = (const int32_t *)(ws + L.off_tfirst);
-    p.Qg = (double *)a.scratch;
+    p.Qg = a.scratch;
     p.Wg = a.scratch + 2 * a.st_stride;
     p.aborted = hdr + 7;
     p.chunk = chunk;
@@ -725,7 +725,7 @@ int run_split_device(const dpf::SolveArgs &a0, const SolveLayout &L, char *ws, c
     p.bar = (int32_t *)(ws + L.off_bar);
     p.part = (double2 *)(ws + L.off_part);
     p.first = (const int32_t *)(ws + L.off_tfirst);
-    p.Qg = (double *)a.scratch;
+    p.Qg = a.scratch;
     p.Wg = a.scratch + 2 * a.st_stride;
     p.aborted = hdr + 7;
     p.first_limit = (int64_t)(route.tail_first_wait_s * 1e9 / dev.ns_per_tick);

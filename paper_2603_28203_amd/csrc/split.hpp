@@ -68,7 +68,7 @@ struct SplitArgs {
     int64_t slice;        // wall-clock ticks per launch, 0 = no limit
     int32_t *bar;         // [n_list][kBarStride] arrival counters (first word of each), zero at launch
     double2 *part;        // [first[n_list]] member partials (loss sum, max|r|), team k at first[k]
-    double *Qg;           // [B][ld] Im(V conj(I)) of the A sweep
+    double2 *Qg;          // [B][ld] entries of which kept_values holds Im(V conj(I)) of the A sweep
     double2 *Wg;          // [B][ld] exchanged w
     int32_t *aborted;     // set when a team abandoned a barrier
     int64_t first_limit;  // wall-clock ticks a member waits at the first barrier
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
     double *__restrict__ ma_c = a.st + a.st_stride + cb;
     double *__restrict__ sv_c = a.st + 2 * a.st_stride + cb;
     double *__restrict__ sa_c = a.st + 3 * a.st_stride + cb;
-    double *__restrict__ Qg = p.Qg + cb;
+    double *__restrict__ Qg = kept_values(p.Qg, cb);
     double2 *__restrict__ Wg = p.Wg + cb;
     const double2 *__restrict__ Sc = a.s_spec + (int64_t)c * a.s_ld;
     const int32_t *__restrict__ swidth = a.sell.width;

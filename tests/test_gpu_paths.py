@@ -390,3 +390,33 @@ def test_paired_kernel_beside_the_multi_workgroup_path(dpf, J):
     rng = np.random.default_rng(50000 + J)
     grids = [random_grid(rng, n, int(1.5 * n)) for n in (900, 400, 700, 60, 300)]
     check_mixed_call(dpf, 50010 + J, grids, 3, 40, 500, "banded-pair", J)
+
+
+def local_grid(rng, n, n_pv):
+    """Random tree plus chords between near buses, in a numbering of bandwidth below 80."""
+    k = np.arange(1, n)
+    f = np.concatenate([k - 1 - rng.integers(0, np.minimum(k, 60)), k[:n // 2]])
+    t = np.concatenate([k, np.minimum(k[:n // 2] + rng.integers(2, 80, n // 2), n - 1)])
+    f, t = f[f != t].astype(np.int32), t[f != t].astype(np.int32)
+    nb = len(f)
+    bt = np.zeros(n, np.int8)
+    kinds = rng.permutation(n)
+    bt[kinds[0]] = 2
+    bt[kinds[1:1 + n_pv]] = 1
+    va = rng.uniform(-0.1, 0.1, n)
+    va[kinds[0]] = 0.0
+    return synth.Grid(n, f, t, rng.uniform(0.01, 0.1, nb), rng.uniform(0.05, 0.3, nb), rng.uniform(0, 0.05, nb), bt,
+                      rng.uniform(0.97, 1.03, n), va)
+
+
+@pytest.mark.parametrize("kind,J,sizes,cap,B,steps", [
+    ("banded-stream", 2, ((600, 90), (400, 60), (450, 0), (800, 100)), 500, 3, 60),
+    ("banded-stream", 4, ((600, 90), (400, 60)), 500, 2, 60),
+    ("banded-pair", 4, ((9800, 1500), (9300, 3700)), 9500, 2, 6)])
+def test_banded_items_keep_their_values_apart_from_the_multi_workgroup_path(dpf, kind, J, sizes, cap, B, steps):
+    """What the banded kernels keep between their sweeps (the paired one where its LDS has
+    no room: 9300 buses with 3700 PV rows) lies in the items' own scratch, beside larger
+    sub-grids, listed first and in between, that the multi-workgroup path solves at the
+    same time."""
+    rng = np.random.default_rng(51000 + J)
+    check_mixed_call(dpf, 51010 + J, [local_grid(rng, *s) for s in sizes], B, steps, cap, kind, J)
