@@ -1092,13 +1092,15 @@ __device__ __forceinline__ double *kept_values(double2 *scratch, int64_t row) {
 // conj(G) V = conj(a) s + h V, s = V conj(I): at a PQ row the seed a holds the whole
 // residual, s = S_spec + (m/2) a; at a PV row a is real and only Im s = qv is needed,
 // 8 B kept between the sweeps where I was 16 (the paired kernel keeps it in LDS, for the
-// PV rows only).  a = w V / |V|^2.
+// PV rows only).  a = w V / |V|^2; a PV row held at |V| = 0 has w = 0 and no angle to
+// move, and gets 0 instead of 0 / 0 (a PQ row there has no direction: NaN, see grad_vm).
 struct SeedTerm {
     double vm, va;
 };
 __device__ __forceinline__ SeedTerm gradient_of_row(double2 w, double2 h, double vm, double cs, double sn, double2 sp,
                                                     double qv, double half_m, bool pq) {
-    const double iv = 1.0 / vm;
+    double iv = 1.0 / vm;
+    if (!pq && isinf(iv)) iv = 0.0;
     const double2 e = make_double2(cs, sn);
     double2 a = cscale(iv, cmul(w, e));
     if (!pq) a.y = 0.0;

@@ -420,3 +420,33 @@ def test_banded_items_keep_their_values_apart_from_the_multi_workgroup_path(dpf,
     same time."""
     rng = np.random.default_rng(51000 + J)
     check_mixed_call(dpf, 51010 + J, [local_grid(rng, *s) for s in sizes], B, steps, cap, kind, J)
+
+
+@pytest.mark.parametrize("path", ["default", "streaming", "banded-stream", "banded-pair", "split", "teams", "wide"])
+def test_pv_bus_at_zero_magnitude_stays_finite(dpf, path):
+    """A PV bus held at |V| = 0 has an angle that moves nothing: its gradient is zero (no
+    0/0), and the other buses follow the oracle on every path."""
+    rng = np.random.default_rng(52000)
+    n, B, steps = 700, 3, 6
+    g = local_grid(rng, n, 90)
+    pv = np.flatnonzero(g.bus_type == 1)[40]
+    S = oracle.injections(oracle.ybus_of(g), g.vm, g.va) * 0.98
+    vm0 = g.vm[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type == 0)
+    va0 = g.va[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type != 2)
+    vm0[:, pv] = 0.0
+    route = {"default": None, "teams": dpf.Route(team_cap=300), "wide": dpf.Route(team_cap=300, wide_host=1)}.get(path)
+    if path not in ("default", "teams", "wide"):
+        kind = "banded-pair" if path == "split" else path
+        route = dpf.Route(variant=next(v["index"] for v in dpf.variants() if v["kind"] == kind))
+    if path == "split":  # handed over after 32 iterations
+        route.tail_handoff, route.tail_team, steps = B, 8, 36
+    vm, va = cu(vm0), cu(va0)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    out = dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm, va, route=route,
+                    opts=dpf.Options(lr=1e-4, tol=0.0, max_iter=steps))
+    assert out["iters"].tolist() == [steps] * B and out["status"].tolist() == [1] * B
+    assert (va[:, pv].cpu().numpy() == va0[:, pv]).all()
+    ref = oracle.solve_adam(oracle.ybus_of(g), g.bus_type, S, vm0[1], va0[1],
+                            oracle.AdamOptions(lr=1e-4, tol=0.0, max_iter=steps))
+    assert np.abs(vm[1].cpu().numpy() - ref["vm"]).max() < TOL
+    assert np.abs(va[1].cpu().numpy() - ref["va"]).max() < TOL
