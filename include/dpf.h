@@ -543,7 +543,9 @@ int32_t dpf_solve_max_sub_buses(void);
  * smallest variant that holds them) and item counts into buckets (<= 64, <= 256,
  * more); dpf_autotune_set records, for the class of n_max, which variant to use
  * instead -- a project-side autotuner times the eligible variants on real inputs
- * (each probe names its variant in its route) and stores the fastest.  Without a
+ * (each probe names its variant in its route) and stores the fastest.  A recorded
+ * register-resident variant of more than 2048 buses serves calls of one grid without a
+ * tail handoff; the others of its class pass over it.  Without a
  * recorded choice, items above 2048 buses that fill at most half of the device
  * (items <= compute units / 2) are spread over several workgroups each (the
  * persistent teams, or the multi-workgroup path with route.wide_host = 1; the
@@ -569,7 +571,7 @@ int32_t dpf_solve_max_sub_buses(void);
  *   dpf_solve_variant_cases : cases per workgroup of a variant (1 for every
  *                             variant), DPF_EINVAL for a bad index
  *   dpf_solve_variant_for   : variant index dpf_solve_batch would use for many
- *                             items, -1 if none
+ *                             items of one grid without a tail handoff, -1 if none
  *   dpf_solve_variant_for_items : the same for `items` work items
  *   dpf_autotune_set        : record `variant` for every item bucket of the class
  *                             of n_max; DPF_EINVAL if it cannot hold n_max buses

@@ -521,6 +521,9 @@ class DPFLoss(torch.autograd.Function):
 
 
 VARIANT_KINDS = ("register", "streaming", "banded-stream", "wide", "banded-pair")
+# register variants of more rows (threads x buses per thread) serve calls of one grid only;
+# a recorded one is passed over by calls of several sub-grids or with a tail handoff
+REGISTER_ROWS_OF_ANY_CALL = 2048
 # the per-item kinds that can hand their tail over (dpf_route_t.tail_handoff)
 HANDOFF_KINDS = ("streaming", "banded-stream", "banded-pair")
 
@@ -602,7 +605,8 @@ def autotune(grid: DeviceGrid, bus_type, s_spec, vm, va, *, outage=None, sub_off
     count as equal and the first of them in the table is taken, which keeps the
     choice stable under timing noise.  With a tail handoff in ``route``, a
     single-grid call chooses among the kinds that can hand over (streaming,
-    banded-stream, banded-pair): the fixed-length probes cannot see the handoff.
+    banded-stream, banded-pair): the fixed-length probes cannot see the handoff.  A
+    call of several sub-grids chooses among the variants that such calls run.
     Returns {variant: seconds}."""
     opts = opts or Options()
     route = route or Route()
@@ -616,6 +620,10 @@ def autotune(grid: DeviceGrid, bus_type, s_spec, vm, va, *, outage=None, sub_off
         kinds = {v["index"]: v["kind"] for v in variants()}
         can = {i: t for i, t in times.items() if kinds[i] in HANDOFF_KINDS}
         eligible = can or times
+    if sub_offset is not None and len(sub_offset) > 2:
+        single = {v["index"] for v in variants() if v["kind"] == "register"
+                  and v["threads"] * v["buses_per_thread"] > REGISTER_ROWS_OF_ANY_CALL}
+        eligible = {i: t for i, t in eligible.items() if i not in single}
     best = min(eligible.values())
     pick = min(i for i, t in eligible.items() if t <= best * (1.0 + tie))
     _check(lib().dpf_autotune_set_items(n_max, items, pick))

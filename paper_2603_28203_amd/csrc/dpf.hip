@@ -267,7 +267,9 @@ int wide_variant_index() {
 
 // forced >= 0: the call's route names the variant (nullptr if it cannot hold n_max).
 // *few_large: the multi-workgroup path was chosen by default for few large items
-// (not from the autotune cache or the route)
+// (not from the autotune cache or the route).  small_only (see default_variant_index)
+// passes over a recorded resident variant too: the record is shared by every call of its
+// size class, whichever kind of call it was made for.
 const Variant *pick_variant(int32_t n_max, int64_t items, int n_cu, int forced = -1, bool *few_large = nullptr,
                             bool small_only = false) {
     int cnt = 0;
@@ -280,7 +282,7 @@ const Variant *pick_variant(int32_t n_max, int64_t items, int n_cu, int forced =
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         const int c = g_tune_init ? g_tune[size_class][items_bucket(items)] : -1;
-        if (c >= 0 && c < cnt && variant_fits(t[c], n_max)) return &t[c];
+        if (c >= 0 && c < cnt && variant_fits(t[c], n_max) && !(small_only && t[c].resident)) return &t[c];
     }
     if (n_max > kWideDefaultBuses && items <= n_cu / 2) {
         if (few_large) *few_large = true;

@@ -196,6 +196,55 @@ def test_route_tail_handoff_sizes_its_own_call_only(lib):
             lib.dpf_solve_workspace_bytes(ctypes.byref(g), 2, sub, 1024, 9241, ctypes.byref(plain_r)))
 
 
+def test_recorded_choice_of_one_grid_calls_leaves_other_calls_alone(lib):
+    """A register-resident variant recorded for 2049 to 4096 buses serves calls of one
+    grid.  It cannot hand its items over and is not for sub-grids of many sizes: calls with
+    a tail handoff or of several sub-grids keep their own kernels, and so their workspace."""
+    _ws_types(lib)
+    g = _Grid(3000, 12000, 10, 1, 1, 1, 0, None, None, None, None, None)
+    gs = _Grid(3900, 12000, 10, 1, 1, 1, 0, None, None, None, None, None)
+    sub = (ctypes.c_int32 * 4)(0, 3000, 3500, 3900)
+    hand = _default_route(lib)
+    hand.tail_handoff = 64
+
+    def sizes():
+        return (lib.dpf_solve_workspace_bytes(ctypes.byref(g), 1, None, 1024, 3000, ctypes.byref(hand)),
+                lib.dpf_solve_workspace_bytes(ctypes.byref(gs), 3, sub, 1024, 3900, None))
+
+    lib.dpf_autotune_reset()
+    resident = lib.dpf_solve_variant_for(3000)
+    assert _kind(lib, resident) == 0
+    want = sizes()
+    try:
+        assert lib.dpf_autotune_set(3000, resident) == 0
+        assert sizes() == want
+        assert lib.dpf_solve_variant_for(3000) == resident
+    finally:
+        lib.dpf_autotune_reset()
+
+
+def test_autotune_of_several_sub_grids_records_what_such_calls_run(lib, monkeypatch):
+    """The autotuner, given timings in which a resident variant is the fastest, records it
+    for a call of one grid and the next fastest for a call of several sub-grids."""
+    from types import SimpleNamespace
+
+    from paper_2603_28203_amd import binding
+
+    rows = {v["index"]: v["threads"] * v["buses_per_thread"] for v in binding.variants() if v["kind"] == "register"}
+    resident = max(rows, key=rows.get)
+    stream = next(v["index"] for v in binding.variants() if v["kind"] == "streaming")
+    assert rows[resident] > binding.REGISTER_ROWS_OF_ANY_CALL
+    monkeypatch.setattr(binding, "_time_variants", lambda *a: a[-2].update({resident: 1.0, stream: 2.0}))
+    vm = SimpleNamespace(shape=(1024, 3500))
+    call = (SimpleNamespace(n_bus=3500), None, None, vm, vm)
+    try:
+        assert binding.autotune(*call)["choice"] == resident
+        assert binding.autotune(*call, sub_offset=[0, 3500])["choice"] == resident
+        assert binding.autotune(*call, sub_offset=[0, 3000, 3500])["choice"] == stream
+    finally:
+        binding.autotune_reset()
+
+
 def test_bad_outage_status_is_declared():
     """An outage index that is neither -1 nor a branch index is reported per case
     (DPF_BAD_OUTAGE, status 4), and the binding exposes the same code."""
