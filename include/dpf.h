@@ -540,7 +540,9 @@ int32_t dpf_solve_max_sub_buses(void);
  * variant (workgroup size, buses per thread, register-resident or streaming
  * state) from the largest sub-grid of the call and the number of work items,
  * unless the call's route names one.  Sizes are grouped into classes (the
- * smallest variant that holds them) and item counts into buckets (<= 64, <= 256,
+ * smallest register-resident variant that holds them up to 2048 buses, one class
+ * above; a choice that cannot hold a size of its class leaves that size its
+ * default) and item counts into buckets (<= 64, <= 256,
  * more); dpf_autotune_set records, for the class of n_max, which variant to use
  * instead -- a project-side autotuner times the eligible variants on real inputs
  * (each probe names its variant in its route) and stores the fastest.  A recorded

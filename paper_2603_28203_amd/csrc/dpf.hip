@@ -226,8 +226,10 @@ bool variant_fits(const Variant &v, int32_t n_max) {
     return dpf::is_banded(v.mode) || v.mode == dpf::kWide || v.k == 0 || (int64_t)n_max <= (int64_t)v.nt * v.k;
 }
 
-// Autotune cache: (size class = index of the default variant, number-of-items
-// bucket) -> chosen variant.  Items buckets: <= 64, <= 256, more.
+// Autotune cache: (size class, number-of-items bucket) -> chosen variant.  The class is
+// the index of the first variant that holds the size among those of any call: one for
+// each register kernel up to 2048 buses, one for everything above.  Items buckets: <= 64,
+// <= 256, more.
 constexpr int kItemBuckets = 3;
 std::mutex g_tune_mu;
 int g_tune[64][kItemBuckets];
@@ -275,7 +277,7 @@ const Variant *pick_variant(int32_t n_max, int64_t items, int n_cu, int forced =
     int cnt = 0;
     const Variant *t = variant_table(&cnt);
     const int d = default_variant_index(n_max, small_only);
-    const int size_class = default_variant_index(n_max);
+    const int size_class = default_variant_index(n_max, true);
     if (few_large) *few_large = false;
     if (d < 0) return nullptr;
     if (forced >= 0) return forced < cnt && variant_fits(t[forced], n_max) ? &t[forced] : nullptr;
@@ -1223,7 +1225,7 @@ static int autotune_store(int32_t n_max, int64_t items, int variant, bool all_bu
     g_err.clear();
     int cnt = 0;
     const Variant *t = variant_table(&cnt);
-    int d = default_variant_index(n_max);
+    const int d = default_variant_index(n_max, true);  // size class
     if (d < 0) return fail(DPF_EINVAL, "no variant holds a sub-grid of this size");
     if (variant < 0 || variant >= cnt || !variant_fits(t[variant], n_max))
         return fail(DPF_EINVAL, "variant cannot hold a sub-grid of this size");

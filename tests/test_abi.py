@@ -223,6 +223,34 @@ def test_recorded_choice_of_one_grid_calls_leaves_other_calls_alone(lib):
         lib.dpf_autotune_reset()
 
 
+def test_sizes_above_the_register_kernels_share_one_class(lib):
+    """A choice recorded for any size above 2048 buses serves every size above 2048 that its
+    variant holds; the others keep their default."""
+    kinds = [_kind(lib, i) for i in range(lib.dpf_solve_variant_count())]
+    pair = kinds.index(4)
+    lib.dpf_autotune_reset()
+    default = {n: lib.dpf_solve_variant_for(n) for n in (1354, 2049, 3000, 4096, 5000, 9241)}
+    assert kinds[default[3000]] == 0 and kinds[default[5000]] == 1
+    try:
+        for recorded in (3000, 5000, 9241):
+            lib.dpf_autotune_reset()
+            assert lib.dpf_autotune_set(recorded, pair) == 0
+            for n in (2049, 3000, 4096, 5000, 9241):
+                assert lib.dpf_solve_variant_for(n) == pair, (recorded, n)
+            assert lib.dpf_solve_variant_for(1354) == default[1354]
+        lib.dpf_autotune_reset()
+        assert lib.dpf_autotune_set(2049, default[2049]) == 0  # holds 2049 and 3000 buses, not the others
+        for n in default:
+            assert lib.dpf_solve_variant_for(n) == default[n], n
+        # the bucket of an item count alone
+        lib.dpf_autotune_reset()
+        assert lib.dpf_autotune_set_items(5000, 256, pair) == 0
+        assert lib.dpf_solve_variant_for_items(3000, ctypes.c_int64(200)) == pair
+        assert lib.dpf_solve_variant_for_items(3000, ctypes.c_int64(300)) == default[3000]
+    finally:
+        lib.dpf_autotune_reset()
+
+
 def test_autotune_of_several_sub_grids_records_what_such_calls_run(lib, monkeypatch):
     """The autotuner, given timings in which a resident variant is the fastest, records it
     for a call of one grid and the next fastest for a call of several sub-grids."""
