@@ -170,11 +170,14 @@ struct Variant {
     int mode;
     KernelFn fn;
     bool resident = false;  // kReg above 2048 buses: a*I in the scratch when the LDS is short
+    KernelFn fn_many = nullptr;  // for calls of many unlike sub-grids (CallPlan::many), where it differs
+    KernelFn kernel(bool many) const { return many && fn_many ? fn_many : fn; }
 };
 
 template <int NT, int K>
 Variant make_variant() {
-    return Variant{NT, K, dpf::kReg, dpf::team_solve_reg_kernel<NT, K>};
+    return Variant{NT, K, dpf::kReg, dpf::team_solve_reg_kernel<NT, K>, false,
+                   K > 1 ? dpf::team_solve_reg_kernel<NT, K, (K > 1)> : nullptr};
 }
 // the same for sub-grids above the register kernels' 2048 buses
 template <int NT, int K>
@@ -299,6 +302,10 @@ struct CallPlan {
     int32_t cap = 0;
     int32_t n_max = 0;  // largest sub-grid <= cap
     bool has_small = false;
+    // sub-grids mostly well below the largest and more items than run side by side: the
+    // register kernels then skip the rows a wave has none of, which costs 1 to 5% of an item
+    // that has all of them (in the comment of team_solve_reg_kernel)
+    bool many = false;
     const Variant *v = nullptr;
     int32_t handoff = 0;  // tail handoff threshold for this call (0 = none)
     bool split_direct = false;  // every item on the split kernel from its first iteration
@@ -1403,17 +1410,20 @@ static CallPlan plan_call(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub
     CallPlan p;
     p.route = route;
     p.cap = max_sub_buses_for(dev, route.team_cap);
-    int64_t small = 0;
+    int64_t small = 0, small_rows = 0;
     for (int32_t s = 0; s < (sub_offset ? n_sub : 1); ++s) {
         const int32_t ns = sub_offset ? sub_offset[s + 1] - sub_offset[s] : g->n_bus;
         if (ns <= p.cap) {
             ++small;
+            small_rows += ns;
             p.n_max = std::max(p.n_max, ns);
         }
     }
     p.has_small = small > 0;
     bool few_large = false;
-    p.v = pick_variant(std::max(1, p.n_max), (int64_t)B * small, dev.n_cu > 0 ? dev.n_cu : 256, route.variant,
+    const int n_cu = dev.n_cu > 0 ? dev.n_cu : 256;
+    p.many = B * small > 2 * n_cu && 4 * small_rows <= 3 * small * p.n_max;
+    p.v = pick_variant(std::max(1, p.n_max), (int64_t)B * small, n_cu, route.variant,
                        &few_large, route.tail_handoff > 0 || (sub_offset && n_sub > 1));
     if (forced_bad) *forced_bad = route.variant >= 0 && !p.v;
     // few large items of one grid that the split kernel can hold, with the split
@@ -1718,9 +1728,9 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
         if (pairs)
             hipLaunchKernelGGL(dpf::pair_in_kernel, pgrid, dim3(256), 0, st, g->n_bus, (int64_t)ld, B, skip, vm, va,
                                a.st, a.st_stride, a.st_fresh, P, P + a.st_stride, P + 2 * a.st_stride);
-        DPF_HIP(hipFuncSetAttribute((const void *)v->fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds_bytes));
-        hipLaunchKernelGGL(v->fn, dim3(items), dim3(v->nt), lds_bytes, st, a);
+        const KernelFn fn = v->kernel(plan.many);
+        DPF_HIP(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
+        hipLaunchKernelGGL(fn, dim3(items), dim3(v->nt), lds_bytes, st, a);
         DPF_HIP(hipGetLastError());
         // the pairs back to the caller's layout (every item of this path, paused ones
         // included) before any other path reads the state
@@ -1735,9 +1745,10 @@ int dpf_solve_batch(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub_offse
             dpf::SolveArgs b = a;
             b.band_nt = v->nt * v->k;  // the banded block
             b.lds_cap = lds_units(*f);
-            DPF_HIP(hipFuncSetAttribute((const void *)f->fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+            const KernelFn f_fn = f->kernel(plan.many);
+            DPF_HIP(hipFuncSetAttribute((const void *)f_fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                         b.lds_cap * 16));
-            hipLaunchKernelGGL(f->fn, dim3(items), dim3(f->nt), (size_t)b.lds_cap * 16, st, b);
+            hipLaunchKernelGGL(f_fn, dim3(items), dim3(f->nt), (size_t)b.lds_cap * 16, st, b);
             DPF_HIP(hipGetLastError());
         }
     }

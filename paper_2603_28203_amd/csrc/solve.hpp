@@ -350,7 +350,18 @@ inline int32_t reg_lds_units(int nt, int32_t n_max, int64_t entries, int32_t lds
         1, std::min<int64_t>(2 * (int64_t)n_max + (entries * 9 + 7) / 8, std::min<int64_t>(share, lds_units)));
 }
 
-template <int NT, int K>
+//
+// MANY: calls of many sub-grids well below the largest.  The row loops skip what a wave
+// has no row for (a scalar branch per row); without that an item of one row per thread
+// pays the updates of all K.  us of 40 iterations, plain -> skipping: the largest of 2000
+// buses and 199 of up to 500, 4 cases 901 -> 592; 1500 and up to 375 716 -> 478; 300 and up
+// to 75, 300 grids 404 -> 331.  Where every item has all rows, or the call ends with its
+// largest item, the branches cost: 2000 buses and 99 to 399 of 100, 100 iterations
+// 1030..1051 -> 1077..1092 (599 of them 1516 -> 1112); 1000 and 299 of 1000, 2 cases
+// 2493 -> 2534 (of 700 1212 -> 1117).  The line lies at two items per CU and a mean size of
+// three quarters of the largest (2000 and 299 of 1500: 4422 -> 4365, 500 and 399 of 400:
+// 878 -> 901).
+template <int NT, int K, bool MANY = false>
 __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
     extern __shared__ double2 X[];
     __shared__ double red[2][NT / kWave];
@@ -458,10 +469,12 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
     // cos and sin of every row's angle and V to LDS: near zero for all rows at once, then
     // the rows of other angles, if the wave has any, one at a time in one rolled loop (the
     // general reduction inlined once instead of once per row)
+    auto has_row = [&](int k) { return !MANY || wv * kWave + k * NT < n; };  // in this wave
     auto publish = [&]() {
         bool far = false;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
+            if (!has_row(k)) break;
             near_sincos(va[k], sn[k], cs[k]);
             far |= !angle_is_near(va[k]);
         }
@@ -574,6 +587,7 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int il = tid + k * NT;
+                if (!has_row(k)) break;
                 double2 sp = make_double2(0.0, 0.0);
                 if constexpr (SREG) sp = S[k];
                 else if (il < n) sp = a.s_spec[sb + opaque_index(row[k])];
@@ -600,6 +614,7 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
             double gv[K], ga[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
+                if (!has_row(k)) break;
                 const double2 h = product(k, wofs);
                 const double2 G = make_double2(aI[k].x + h.x, aI[k].y - h.y);
                 gv[k] = grad_vm(G, cs[k], sn[k], vm[k]);
@@ -620,6 +635,7 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
             sc = nx;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
+                if (!has_row(k)) break;
                 double vmn = vm[k], van = va[k];
                 opt_update2(os, vmn, gv[k], mv[k], sv[k], van, ga[k], ma[k], sa[k]);
                 vm[k] = (pq >> k) & 1u ? vmn : vm[k];

@@ -450,3 +450,36 @@ def test_pv_bus_at_zero_magnitude_stays_finite(dpf, path):
                             oracle.AdamOptions(lr=1e-4, tol=0.0, max_iter=steps))
     assert np.abs(vm[1].cpu().numpy() - ref["vm"]).max() < TOL
     assert np.abs(va[1].cpu().numpy() - ref["va"]).max() < TOL
+
+
+@pytest.mark.parametrize("top,sizes", [(2048, (65, 64, 512, 513, 1024, 2, 1100)), (1500, (2, 512, 700, 63, 300)),
+                                       (900, (129, 512, 40)), (300, (257, 3, 100, 256, 30))])
+def test_many_unlike_sub_grids_on_the_register_kernels(dpf, top, sizes):
+    """Calls of many sub-grids well below the largest skip the rows a wave has none of: every
+    item, from two buses to all rows of every thread, follows the oracle, with optimizer
+    state in and out."""
+    rng = np.random.default_rng(53000 + top)
+    sizes = (top,) + sizes
+    B, steps = 514 // len(sizes) + 1, 5  # more items than two per CU of 256
+    grids = [random_grid(rng, n, int(1.5 * n) if n > 9 else n - 1) for n in sizes]
+    off, branches, bt = collection(grids)
+    n = off[-1]
+    S = np.concatenate([oracle.injections(oracle.ybus_of(g), g.vm, g.va) for g in grids]) * 0.98
+    vm0 = np.concatenate([g.vm for g in grids])[None] + rng.normal(0, 1e-2, (B, n)) * (bt == 0)
+    va0 = np.concatenate([g.va for g in grids])[None] + rng.normal(0, 1e-2, (B, n)) * (bt != 2)
+    va0[1] += 2.5 * (bt != 2)
+    vm, va = cu(vm0), cu(va0)
+    state = torch.zeros(4, B, n, dtype=torch.float64, device="cuda")
+    sched = dpf.fresh_sched_state(B * len(sizes), 1e-3)
+    Yg = dpf.build_ybus(n, *branches)
+    for part in (2, steps - 2):
+        out = dpf.solve(Yg, bt, cu(S, torch.complex128), vm, va, sub_offset=off, adam_state=state, sched_state=sched,
+                        opts=dpf.Options(lr=1e-3, tol=0.0, max_iter=part))
+    assert (out["iters"] == steps - 2).all()
+    for k, g in enumerate(grids):
+        sl = slice(off[k], off[k + 1])
+        for c in (0, 1, B - 1):
+            ref = oracle.solve_adam(oracle.ybus_of(g), g.bus_type, S[sl], vm0[c, sl], va0[c, sl],
+                                    oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=steps))
+            assert np.abs(vm[c, sl].cpu().numpy() - ref["vm"]).max() < TOL, (k, c)
+            assert np.abs(va[c, sl].cpu().numpy() - ref["va"]).max() < TOL, (k, c)
