@@ -483,3 +483,117 @@ def test_many_unlike_sub_grids_on_the_register_kernels(dpf, top, sizes):
                                     oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=steps))
             assert np.abs(vm[c, sl].cpu().numpy() - ref["vm"]).max() < TOL, (k, c)
             assert np.abs(va[c, sl].cpu().numpy() - ref["va"]).max() < TOL, (k, c)
+
+
+def run_both_ways(dpf, g, S, vm0, va0, opts, route, parts):
+    """One call and the same iterations in several calls that continue each other through
+    the caller's optimizer and schedule state: equal bit for bit; returns the one call's
+    (vm, va, schedule, outputs)."""
+    B, n = vm0.shape
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    got = []
+    for split in ([sum(parts)], parts):
+        vm, va = cu(vm0), cu(va0)
+        state, sched = torch.zeros(4, B, n, dtype=torch.float64, device="cuda"), dpf.fresh_sched_state(B, opts["lr"])
+        for k in split:
+            out = dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm, va, adam_state=state, sched_state=sched,
+                            opts=dpf.Options(**opts, tol=0.0, max_iter=k), route=route)
+            assert out["iters"].tolist() == [k] * B
+        got.append((vm, va, sched, state, out["max_mis"], out["loss"]))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    return got[0]
+
+
+@pytest.mark.parametrize("kind,threads,J,n", [("register", 512, 6, 2300), ("register", 512, 8, 3500),
+                                              ("streaming", 1024, 0, 3000)])
+@pytest.mark.parametrize("opt", ["adam-plateau", "adam-step", "sgd-step", "rmsprop-plateau", "rmsprop"])
+def test_named_kernels_above_the_register_sizes(dpf, kind, threads, J, n, opt):
+    """The resident kernels and the streaming kernel, named in the route: every optimizer
+    and schedule against the oracle, resumed from non-zero moments and schedule state, and
+    the stop test at a tolerance the solve reaches."""
+    rng = np.random.default_rng(54000 + n)
+    g = random_grid(rng, n, int(1.4 * n), 12)
+    B = 3
+    S = oracle.injections(oracle.ybus_of(g), g.vm, g.va)
+    vm0 = g.vm[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type == 0)
+    va0 = g.va[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type != 2)
+    o = {"adam": dict(lr=1e-3), "sgd": dict(lr=1e-3, beta1=0.9, optimizer=dpf.OPT_SGD),
+         "rmsprop": dict(lr=1e-3, beta2=0.99, optimizer=dpf.OPT_RMSPROP)}[opt.split("-")[0]]
+    if "plateau" in opt:
+        o.update(sched=dpf.SCHED_PLATEAU, factor=0.5, patience=2, threshold=0.3, cooldown=1)
+    if "step" in opt:
+        o.update(sched=dpf.SCHED_STEP, factor=0.7, patience=3)
+    route = dpf.Route(variant=next(v["index"] for v in dpf.variants() if v["kind"] == kind and v["threads"] == threads
+                                   and v["buses_per_thread"] == J))
+    vm, va, sched, _, mu, _ = run_both_ways(dpf, g, S, vm0, va0, o, route, [5, 4, 5])
+    Yo = oracle.ybus_of(g)
+    for c in (0, B - 1):
+        ref = oracle.solve_adam(Yo, g.bus_type, S, vm0[c], va0[c], oracle.AdamOptions(tol=0.0, max_iter=14, **o))
+        assert np.abs(vm[c].cpu().numpy() - ref["vm"]).max() < TOL, c
+        assert np.abs(va[c].cpu().numpy() - ref["va"]).max() < TOL, c
+        assert sched[c, 1].item() == pytest.approx(ref["lr"], rel=1e-14), c
+        assert abs(mu[c].item() - ref["mu"]) <= TOL * ref["mu"], c
+    # the first of the steps at which max|r| falls below a bound in the widest gap of its way
+    mus = [oracle.solve_adam(Yo, g.bus_type, S, vm0[0], va0[0], oracle.AdamOptions(tol=0.0, max_iter=k, **o))["mu"]
+           for k in range(15)]
+    low = np.minimum.accumulate(mus)
+    k = 1 + int(np.argmax(low[:-1] / low[1:]))
+    tol = np.sqrt(low[k - 1] * low[k])
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    vm, va = cu(vm0[:1]), cu(va0[:1])
+    out = dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm, va, opts=dpf.Options(**o, tol=tol, max_iter=14),
+                    route=route)
+    ref = oracle.solve_adam(Yo, g.bus_type, S, vm0[0], va0[0], oracle.AdamOptions(tol=tol, max_iter=14, **o))
+    assert (out["status"].item(), out["iters"].item()) == (0, k) == (ref["status"], ref["iters"])
+    assert np.abs(vm[0].cpu().numpy() - ref["vm"]).max() < TOL and np.abs(va[0].cpu().numpy() - ref["va"]).max() < TOL
+
+
+@pytest.mark.parametrize("kind", ["banded-stream", "banded-pair"])
+@pytest.mark.parametrize("n", [3000, 3500])
+def test_wide_band_of_a_named_banded_kernel_runs_the_resident_one(dpf, kind, n):
+    """One grid of 2049 to 4096 buses whose bandwidth exceeds the named banded kernel's
+    block (a numbering as in its file) runs on a resident kernel of the same call, a*I in
+    LDS (3000 buses) or in the scratch the banded kernels lay out (3500), with and without
+    the caller's optimizer state."""
+    rng = np.random.default_rng(55000 + n)
+    g = random_grid(rng, n, int(1.4 * n))
+    assert np.abs(g.f - g.t).max() > 2048
+    B = 3
+    S = oracle.injections(oracle.ybus_of(g), g.vm, g.va)
+    vm0 = g.vm[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type == 0)
+    va0 = g.va[None] + rng.normal(0, 1e-2, (B, n)) * (g.bus_type != 2)
+    route = dpf.Route(variant=next(v["index"] for v in dpf.variants() if v["kind"] == kind and v["buses_per_thread"] == 2))
+    vm, va, *_ = run_both_ways(dpf, g, S, vm0, va0, dict(lr=1e-3), route, [4, 5])
+    ref = oracle.solve_adam(oracle.ybus_of(g), g.bus_type, S, vm0[2], va0[2],
+                            oracle.AdamOptions(lr=1e-3, tol=0.0, max_iter=9))
+    assert np.abs(vm[2].cpu().numpy() - ref["vm"]).max() < TOL and np.abs(va[2].cpu().numpy() - ref["va"]).max() < TOL
+    vm2, va2 = cu(vm0), cu(va0)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    dpf.solve(Yg, g.bus_type, cu(S, torch.complex128), vm2, va2, opts=dpf.Options(lr=1e-3, tol=0.0, max_iter=9),
+              route=route)
+    assert torch.equal(vm2, vm) and torch.equal(va2, va)
+
+
+@pytest.mark.parametrize("kind", ["banded-stream", "banded-pair", "split"])
+def test_injections_of_the_librarys_own_evaluation_leave_rounding_residuals(dpf, kind):
+    """The paired, banded and split kernels form V conj(I) - S with S inside the chain of
+    multiply-adds.  Started where S was evaluated by the library itself, a bus's residual is
+    then the rounding of the product, as for injections from anywhere else, and not exactly
+    zero at every bus (which changes the optimizer's path)."""
+    rng = np.random.default_rng(56000)
+    n = 900
+    g = local_grid(rng, n, 120)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    vm0, va0 = cu(g.vm[None]), cu(g.va[None])
+    zero = torch.zeros(n, dtype=torch.complex128, device="cuda")
+    S = dpf.mismatch_grad(Yg, g.bus_type, zero, vm0, va0, want_grad=False)["dS"][0].contiguous()
+    variant = next(v["index"] for v in dpf.variants() if v["kind"] == ("banded-pair" if kind == "split" else kind))
+    route = dpf.Route(variant=variant)
+    mu = dpf.solve(Yg, g.bus_type, S, vm0.clone(), va0.clone(), route=route,
+                   opts=dpf.Options(lr=0.0, tol=0.0, max_iter=0))["max_mis"].item()
+    if kind == "split":  # lr 0 keeps the start; handed over after 32 iterations
+        route.tail_handoff, route.tail_team = 1, 4
+        mu = dpf.solve(Yg, g.bus_type, S, vm0.clone(), va0.clone(), route=route,
+                       opts=dpf.Options(lr=0.0, tol=0.0, max_iter=40))["max_mis"].item()
+    # a product of at most |S| + its share of the row sum rounds by some units of 2^-53
+    assert 0.0 < mu <= 64 * 2.0 ** -53 * S.abs().max().item()
