@@ -145,10 +145,12 @@ def _stream():
 
 
 def _dev(t, dtype, device):
-    if isinstance(t, torch.Tensor) and t.dtype == dtype and t.device == device and t.is_contiguous():
+    """t as a tensor whose memory holds its values in order (a lazy conjugate's does not)."""
+    if isinstance(t, torch.Tensor) and t.dtype == dtype and t.device == device and t.is_contiguous() \
+            and not t.is_conj():
         return t  # nothing to convert (three dispatched calls less)
     t = torch.as_tensor(t)
-    return t.to(device=device, dtype=dtype).contiguous()
+    return t.to(device=device, dtype=dtype).contiguous().resolve_conj()
 
 
 @dataclass
@@ -386,15 +388,12 @@ def solve(grid: DeviceGrid, bus_type, s_spec, vm, va, *, opts: Options | None = 
     B, ld = vm.shape
     if not (vm.is_contiguous() and va.is_contiguous() and vm.dtype == torch.float64 and va.dtype == torch.float64):
         raise ValueError("vm and va must be contiguous float64 tensors (updated in place)")
-    bt = bus_type if (torch.is_tensor(bus_type) and bus_type.dtype == torch.int8 and bus_type.device == dev) \
-        else _dev(bus_type, torch.int8, dev)
-    s = s_spec if (torch.is_tensor(s_spec) and s_spec.dtype == torch.complex128 and s_spec.device == dev
-                   and s_spec.is_contiguous()) else _dev(s_spec, torch.complex128, dev)
+    bt = _dev(bus_type, torch.int8, dev)
+    s = _dev(s_spec, torch.complex128, dev)
     if s.dim() == 2 and s.shape[0] != B:
         raise ValueError(f"s_spec has {s.shape[0]} rows for {B} cases (pass one row per case, or a 1-D shared row)")
     s_ld = 0 if s.dim() == 1 else s.shape[1]
-    out = None if outage is None else (outage if (torch.is_tensor(outage) and outage.dtype == torch.int32
-                                                  and outage.device == dev) else _dev(outage, torch.int32, dev))
+    out = None if outage is None else _dev(outage, torch.int32, dev)
     if sub_offset is None:
         n_sub, so_h, so_d = 1, None, None
     else:
@@ -463,9 +462,8 @@ def solve_series(grid: DeviceGrid, bus_type, s_series, vm0, va0, *, window: int 
     opts = opts or Options()
     dev = s_series.device
     T, n = s_series.shape
-    s = s_series.contiguous()
-    bt = bus_type if (torch.is_tensor(bus_type) and bus_type.dtype == torch.int8 and bus_type.device == dev) \
-        else _dev(bus_type, torch.int8, dev)
+    s = _dev(s_series, torch.complex128, dev)
+    bt = _dev(bus_type, torch.int8, dev)
     vm0 = _dev(vm0, torch.float64, dev)
     va0 = _dev(va0, torch.float64, dev)
     vm = torch.empty((T, n), dtype=torch.float64, device=dev)

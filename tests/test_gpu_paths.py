@@ -597,3 +597,33 @@ def test_injections_of_the_librarys_own_evaluation_leave_rounding_residuals(dpf,
                        opts=dpf.Options(lr=0.0, tol=0.0, max_iter=40))["max_mis"].item()
     # a product of at most |S| + its share of the row sum rounds by some units of 2^-53
     assert 0.0 < mu <= 64 * 2.0 ** -53 * S.abs().max().item()
+
+
+def test_strided_and_lazily_conjugated_inputs_are_read_as_their_values(dpf):
+    """Bus kinds and outages given as a column of a wider tensor, and injections as a lazy
+    conjugate, give what contiguous copies of them give."""
+    rng = np.random.default_rng(57000)
+    n, B = 200, 4
+    g = random_grid(rng, n, 320)
+    Yg = dpf.build_ybus(n, g.f, g.t, g.r, g.x, g.b)
+    S = cu(oracle.injections(oracle.ybus_of(g), g.vm, g.va) * 0.98, torch.complex128)
+    bt = cu(np.stack([g.bus_type, np.roll(g.bus_type, 5)], 1), torch.int8)[:, 0]
+    nbr = synth.non_bridge_branches(n, g.f, g.t)
+    outage = cu(np.stack([rng.choice(nbr, B), np.full(B, -1)], 1), torch.int32)[:, 0]
+    lazy = S.resolve_conj().conj().clone().conj()  # equal to S, its storage conjugated
+    assert lazy.is_conj() and not bt.is_contiguous() and not outage.is_contiguous()
+    vm, va = cu(np.tile(g.vm, (B, 1))), cu(np.tile(g.va, (B, 1)))
+
+    def run(bt, s, out):
+        v, a, d = vm.clone(), va.clone(), torch.zeros_like(va)
+        opts = dpf.Options(lr=1e-3, tol=0.0, max_iter=5)
+        o = dpf.solve(Yg, bt, s, v, a, outage=out, opts=opts)
+        e = dpf.mismatch_grad(Yg, bt, s, vm, va, outage=out)
+        p = dpf.param_grad(Yg, bt, s, vm, va, outage=out)
+        dpf.dc_init(dpf.build_dc_grid(n, g.f, g.t, g.x), bt, s, d, outage=out)
+        t = dpf.solve_series(Yg, bt, s[None].expand(3, n), vm[0], va[0], opts=opts, window=2)
+        return [v, a, d, o["loss"], *(e[k] for k in sorted(e)), *(p[k] for k in sorted(p)), t["vm"], t["va"]]
+
+    for x, y in zip(run(bt.clone(memory_format=torch.contiguous_format), S, outage.clone(memory_format=torch.contiguous_format)),
+                    run(bt, lazy, outage)):
+        assert torch.equal(x, y)
