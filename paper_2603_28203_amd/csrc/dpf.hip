@@ -1433,7 +1433,7 @@ static CallPlan plan_call(const dpf_grid_t *g, int32_t n_sub, const int32_t *sub
         (size_t)p.n_max * 16 + (size_t)(p.n_max + 31) / 32 * 4 + 512 <= (size_t)dev.lds_per_block)
         p.split_direct = true;
     if (p.v && p.v->mode == dpf::kWide) {  // every sub-grid to the multi-workgroup path
-        p.cap = 0;
+        p.cap = -1;  // empty sub-grids too: no other kernel would report them
         p.n_max = 0;
         p.has_small = false;
     }

@@ -627,3 +627,41 @@ def test_strided_and_lazily_conjugated_inputs_are_read_as_their_values(dpf):
     for x, y in zip(run(bt.clone(memory_format=torch.contiguous_format), S, outage.clone(memory_format=torch.contiguous_format)),
                     run(bt, lazy, outage)):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("path", ["default", "streaming", "banded-pair", "wide", "teams", "host", "few-large-host"])
+@pytest.mark.parametrize("tol", [0.0, 1e-6])
+def test_empty_sub_grids_report_like_any_item(dpf, path, tol):
+    """A sub-grid without buses has nothing to learn: every path reports it with a mismatch
+    and loss of 0, converged at once, or after every iteration where the tolerance is 0."""
+    rng = np.random.default_rng(58000)
+    sizes = (2500, 40) if path == "few-large-host" else (300, 40)
+    grids = [random_grid(rng, n, int(1.4 * n)) for n in sizes]
+    off, branches, bt = collection(grids)
+    off = [off[0], off[0], off[1], off[1], off[2], off[2]]
+    B, steps, n = 2, 4, off[-1]
+    S = np.concatenate([oracle.injections(oracle.ybus_of(g), g.vm, g.va) for g in grids])
+    vm0 = np.concatenate([g.vm for g in grids])[None] + rng.normal(0, 1e-2, (B, n)) * (bt == 0)
+    va0 = np.tile(np.concatenate([g.va for g in grids]), (B, 1))
+    kinds = {v["kind"]: v["index"] for v in dpf.variants()}
+    route = {"default": None, "teams": dpf.Route(team_cap=200), "host": dpf.Route(team_cap=200, wide_host=1),
+             "few-large-host": dpf.Route(wide_host=1)}.get(path) or dpf.Route(variant=kinds.get(path, -1))
+    outs = {k: torch.full((B * 5,), -7, dtype=d, device="cuda") for k, d in
+            (("iters", torch.int32), ("status", torch.int32), ("max_mis", torch.float64), ("loss", torch.float64))}
+    vm, va = cu(vm0), cu(va0)
+    Yg = dpf.build_ybus(n, *branches)
+    dpf.solve(Yg, bt, cu(S, torch.complex128), vm, va, sub_offset=off, route=route, outputs=outs,
+              opts=dpf.Options(lr=1e-3, tol=tol, max_iter=steps))
+    got = {k: outs[k].reshape(B, 5).cpu().numpy() for k in ("iters", "status", "max_mis", "loss")}
+    full = [1, 3]
+    assert (got["iters"][:, full] == steps).all() and (got["status"][:, full] == 1).all()
+    empty = [0, 2, 4]
+    assert (got["iters"][:, empty] == (0 if tol > 0 else steps)).all()
+    assert (got["status"][:, empty] == (0 if tol > 0 else 1)).all()
+    assert (got["max_mis"][:, empty] == 0).all() and (got["loss"][:, empty] == 0).all()
+    for k, g in enumerate(grids):
+        sl = slice(off[2 * k + 1], off[2 * k + 2])
+        ref = oracle.solve_adam(oracle.ybus_of(g), g.bus_type, S[sl], vm0[1, sl], va0[1, sl],
+                                oracle.AdamOptions(lr=1e-3, tol=tol, max_iter=steps))
+        assert np.abs(vm[1, sl].cpu().numpy() - ref["vm"]).max() < TOL
+        assert np.abs(va[1, sl].cpu().numpy() - ref["va"]).max() < TOL
