@@ -469,12 +469,14 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
     // cos and sin of every row's angle and V to LDS: near zero for all rows at once, then
     // the rows of other angles, if the wave has any, one at a time in one rolled loop (the
     // general reduction inlined once instead of once per row)
-    auto has_row = [&](int k) { return !MANY || wv * kWave + k * NT < n; };  // in this wave
+    auto has_row = [&](int k) { return wv * kWave + k * NT < n; };  // this wave, MANY
     auto publish = [&]() {
         bool far = false;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (!has_row(k)) break;
+            if constexpr (MANY)
+                if constexpr (MANY)
+                    if (!has_row(k)) break;
             near_sincos(va[k], sn[k], cs[k]);
             far |= !angle_is_near(va[k]);
         }
@@ -587,7 +589,8 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int il = tid + k * NT;
-                if (!has_row(k)) break;
+                if constexpr (MANY)
+                    if (!has_row(k)) break;
                 double2 sp = make_double2(0.0, 0.0);
                 if constexpr (SREG) sp = S[k];
                 else if (il < n) sp = a.s_spec[sb + opaque_index(row[k])];
@@ -614,7 +617,8 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
             double gv[K], ga[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                if (!has_row(k)) break;
+                if constexpr (MANY)
+                    if (!has_row(k)) break;
                 const double2 h = product(k, wofs);
                 const double2 G = make_double2(aI[k].x + h.x, aI[k].y - h.y);
                 gv[k] = grad_vm(G, cs[k], sn[k], vm[k]);
@@ -635,7 +639,8 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
             sc = nx;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                if (!has_row(k)) break;
+                if constexpr (MANY)
+                    if (!has_row(k)) break;
                 double vmn = vm[k], van = va[k];
                 opt_update2(os, vmn, gv[k], mv[k], sv[k], van, ga[k], ma[k], sa[k]);
                 vm[k] = (pq >> k) & 1u ? vmn : vm[k];
