@@ -215,9 +215,10 @@ __device__ __forceinline__ void fast_sum2(double &a, double &b, double2 *red) {
 // or are read from the CSR when they do not fit.  Three barriers per step.
 // Bound by the latency of a step (two reductions, two divisions, the gathers), where the
 // form above, with its vectors in global memory, waited for about ten dependent trips to
-// L2.  us per step on an MI355X, above -> this: 118 buses 4.0 -> 1.15, 500 5.0 -> 1.35,
-// 1354 x 64 cases 7.7 -> 1.75, 3000 12.6 -> 3.0, 4000 16.1 -> 4.4 (4 entries of a row in
-// registers; with none and the CSR for the rest, as above 4096 buses, 11.1), 8000 33 -> 22.
+// L2.  us per step on an MI355X, above -> this: 118 buses 3.8 -> 0.9, 500 5.1 -> 1.3,
+// 1354 x 64 cases 8.6 -> 1.75, 3000 13.5 -> 3.2, 4000 16.9 -> 10.0 (4 entries of a row in
+// registers; the rest of this grid's rows exceeds the LDS and comes from the CSR: 4.4 on
+// one whose rows fit), 8000 31 -> 29 (no entries in registers).
 // 512 threads up to 4096 buses: the registers of 1024 hold 4 rows without entries.
 constexpr int kDcMaxRows = 8 * 1024;  // rows: 16-bit byte offsets, and slices of one wave scan
 

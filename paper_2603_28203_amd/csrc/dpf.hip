@@ -241,15 +241,16 @@ bool g_tune_init = false;
 int items_bucket(int64_t items) { return items <= 64 ? 0 : (items <= 256 ? 1 : 2); }
 
 // Items larger than this (buses) that fill at most half of the chip (2 items <= CUs)
-// are solved faster spread over several workgroups than one workgroup each (measured
-// on the persistent teams: 9241 buses, 64 cases, 38 against 68 us per iteration; 1354
-// buses: one workgroup wins; 3000 buses: 64 cases 9.5 us on teams against 14.6 on the
-// resident kernel, 256 cases, one per CU, 39 against 14.6).
+// are solved faster spread over several workgroups than one workgroup each.  us per
+// iteration, persistent teams against the best kernel of one workgroup per item: 9241
+// buses, 1 case 7.9 / 51, 64 cases 24.6 / 56, 128 cases 40 / 61; 3000 buses, 64 cases
+// 8.0 / 13.2 (128 cases, where the line does not fit, 17.0 / 13.2); 1950 buses, 64 cases
+// 7.6 / 8.1; 1354 buses, 1 to 128 cases 6.4 to 7.5 / 5.1.
 constexpr int32_t kWideDefaultBuses = 2048;
 
 // first register-resident variant that holds n_max buses, else the streaming one
 // (256 cases, us per iteration on the resident kernels against streaming: 2500 buses
-// 14.2 / 20, 4000 22.7 / 30.7).  small_only: no register-resident variant above 2048 buses, for calls that may hand
+// 11.9 / 18.9, 4000 19.8 / 29.6).  small_only: no register-resident variant above 2048 buses, for calls that may hand
 // their items over (those kernels cannot) and calls of several sub-grids (their threads
 // carry 6 or 8 rows also for an item of a few)
 int default_variant_index(int32_t n_max, bool small_only = false) {
@@ -964,7 +965,7 @@ int dpf_build_ybus(int32_t n_bus, int32_t n_branch, const int32_t *from, const i
     hipStream_t st = (hipStream_t)stream;
     const YbusTemps T = ybus_temps(n_bus, n_branch);
     // the static array where it is large enough and free (allocating and freeing costs
-    // more than the build: 160 against 60 us for 9241 buses), else memory of its own
+    // about as much as the build), else memory of its own
     if (T.total() <= kYbusScratchBytes) {
         DeviceInfo dev;
         rc = device_info(dev);

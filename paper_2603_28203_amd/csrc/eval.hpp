@@ -287,9 +287,10 @@ struct EvalArgs {
 // before, 64 to 80 B here).  Bound by the chain of matrix load and LDS gather of every
 // row: four lanes sharing a row, 16 rows per load and so a quarter of the cache lines
 // per load, is 4 to 20% slower (1354 x 64 13.1 -> 15.7 us, 9241 x 256 81 -> 97), its
-// gathers and sums being more.  Device time of a call on an
-// MI355X, five launches -> this: 118 buses x 8 cases 14 -> 6 us, 1354 x 64 22.5 -> 13.3
-// (with branch gradients 21.2 -> 10.6), 5000 x 256 120 -> 43, 9241 x 256 241 -> 79.
+// gathers and sums being more.  A call on an MI355X, grids in an arbitrary numbering, five
+// launches -> this: 118 buses x 8 cases 31 -> 15 us (host; its kernels 14 -> 6), 5000 x 256
+// 124 -> 45, 9241 x 256 220 -> 76 (in a small-bandwidth numbering 185 -> 73); kernels with
+// branch gradients, 1354 x 64, 21 -> 10.4.
 template <int NT, int K, bool BOTH>
 __global__ __launch_bounds__(NT) void eval_case_kernel(EvalArgs a) {
     extern __shared__ double2 X[];

@@ -106,7 +106,7 @@ struct SolveArgs {
 // the compiler keeps all of them in scalar registers across the loops, spills 100 to
 // 200 of those to vector lanes, and the FP64 constants end up in vector registers.
 // (The one-row register kernels, whose iteration is one latency chain, take them as
-// ordinary arguments: 1.43 against 1.52 us per iteration of a 14-bus solve.)
+// ordinary arguments: a 14-bus iteration is 6% longer otherwise.)
 typedef const __attribute__((address_space(4))) SolveArgs ColdArgs;
 __device__ __forceinline__ ColdArgs *cold_args() {
     ColdArgs *p = (ColdArgs *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -329,14 +329,15 @@ __device__ __forceinline__ uint32_t opaque_index(uint32_t i) {
 //    learnable keep their value by a select), their two division chains overlapped.
 //  - a single grid's rows are sorted by length (sell_sort_rows), so slices carry next
 //    to no padding in any numbering.
-// Measured on an MI355X, us per iteration, one earlier form of this kernel (matrix from
-// L2, updates one after the other behind the stop test) -> this one: 14 buses x 1 case
-// 2.7 -> 1.5; 118 x 2048 7.3 -> 4.8; 250 x 1024 8.1 -> 4.7; 900 x 512 13.5 -> 8.6;
-// 1354 x 64 8.0 -> 5.5 (9.3 -> 5.6 in an arbitrary numbering); 1950 x 64 11.3 -> 8.7.
+// Measured on an MI355X, us per iteration (the difference of calls of 50 and 250), the
+// form before (matrix from L2, updates one after the other behind the stop test) -> this
+// one: 14 buses x 1 case 2.3 -> 1.3; 118 x 2048 6.7 -> 4.1; 250 x 1024 6.6 -> 4.2;
+// 900 x 512 12.7 -> 7.0; 1354 x 64 7.6 -> 5.1 (8.8 -> 5.1 in an arbitrary numbering);
+// 1950 x 64 11.5 -> 8.0.
 // At three rows per thread the columns and injections are re-read instead of kept
-// (both kept: 94 spilled registers, 5.6 us); at four the matrix stays in global memory
+// (both kept: 94 spilled registers and no gain); at four the matrix stays in global memory
 // (V, w and a 2048-row matrix exceed the LDS).  1024 threads with two rows each spill
-// 150 registers (11 us for 1354 x 64).
+// 150 registers (twice the time for 1354 x 64).
 constexpr int kRegCols = 8;           // columns of a row kept in registers
 constexpr int kRegLdsRows = 3;        // rows per thread up to which the matrix goes to LDS
 constexpr int kRegLdsPerThread = 320; // bytes: 160 KB over the 512 threads two waves per SIMD make
@@ -603,6 +604,10 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
                 lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
                 const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
                 aI[k] = cmul(av, acc);
+                // w = av conj(v), scaled after the product: the same cost as before it, another
+                // rounding.  The step at which a solve of thousands of steps meets its tolerance
+                // hangs on such roundings (the oracle's own does, under 1e-16 changes of its
+                // inputs), so the order stays as the tests of such solves were run with
                 if (il < n) *reinterpret_cast<double2 *>(lds + wofs + il * 16) = cscale(two_over_m, cmulc(make_double2(rP, rQ), v));
             }
             if constexpr (NW > 1) block_reduce2<NT>(lsum, lmax, red);
@@ -682,10 +687,12 @@ __global__ __launch_bounds__(NT) void team_solve_reg_kernel(SolveArgs a) {
 // The streaming kernel moves 176 B of state per bus and iteration through L2 and the
 // Infinity Cache (5.4 TB/s at 256 cases of 3000 buses, its bound); this one moves none
 // and is bound by the latency of its row products (two waves per SIMD, about half of
-// the FP64 issue used).  us per iteration, streaming -> this, 256 cases: 2500 buses
-// 20 -> 14.2, 3000 24.0 -> 14.6, 4000 30.7 -> 22.7 (8 rows per thread; a*I in global
-// memory).  512 threads: 1024 spill 30 to 120 registers (15.0 us at best); gathers of
-// a group of four issued together (one at a time 17.1 us; groups of 6 or 8 16.1, 17.5).
+// the FP64 issue used).  us per iteration, streaming -> this, 256 cases in an arbitrary
+// numbering: 2500 buses 19.5 -> 12.0, 3000 23.4 -> 13.0, 4000 30.9 -> 19.8 (8 rows per
+// thread; a*I in global memory).  Calls of 60 iterations of 256 x 3000, us per iteration
+// with the call's fixed cost: 14.6; 1024 threads, which spill 30 to 120 registers, 15.0 at
+// best; gathers of a group of four one at a time 17.1 instead of together; groups of 6 or 8
+// 16.1, 17.5.
 template <int NT, int K>
 __global__ __launch_bounds__(NT) void team_solve_resident_kernel(SolveArgs a) {
     extern __shared__ double2 X[];
@@ -1092,10 +1099,15 @@ __global__ __launch_bounds__(NT) void team_solve_stream_kernel(SolveArgs a) {
 }
 
 // V conj(I) - S with S inside the chain of multiply-adds: its rounding then differs from
-// that of any S formed as a product before.  A start at such an S (an outage from the
-// base case's own injections) would otherwise leave residuals of exactly zero at most
-// buses, which Adam turns into a longer path: 264 instead of 50 steps at the median to
-// max|r| < 1e-3 on 1024 outages of 9241 buses, 4% more steps to 1e-6.
+// that of any S formed as a product before, and a start at such an S (an outage from the
+// base case's own injections, evaluated by this library) takes about the steps that the
+// same start takes with injections from anywhere else.  With the product formed first, as in
+// the other solve kernels and in these ones before, the residual is exactly zero at most
+// buses and Adam takes another path: on 1024 outages of 9241 buses 264 instead of 50 steps
+// at the median to max|r| < 1e-3 and 4% more to 1e-6; at other settings fewer (300 to 9241
+// buses, lr 1e-4, eps 1e-14: 250..330 instead of 470..690) or none that converge within
+// 2000 (lr 1e-3, eps 1e-8, where this form takes 83..90 up to 3000 buses).  qv, which keeps the product
+// alive beside the residual, would undo a contraction left to the compiler.
 __device__ __forceinline__ double2 residual_of_row(double2 v, double2 i, double2 s) {
     return make_double2(fma(v.x, i.x, fma(v.y, i.y, -s.x)), fma(v.y, i.x, fma(-v.x, i.y, -s.y)));
 }

@@ -122,7 +122,7 @@ __device__ __forceinline__ int load_key(int L) {
 
 // One wave per number of waves w searches its own row target without a barrier (all
 // eight searches one after the other with block-wide sums took 76 us for one grid, 6% of
-// a 100-iteration solve; this kernel 5).
+// a 100-iteration solve; this kernel 8, and 10 for 48 grids).
 static_assert(kPlanThreads == kTeamMaxWaves * kWave, "one wave per w");
 
 __global__ __launch_bounds__(kPlanThreads) void team_plan_kernel(int32_t n_sub, const int32_t *__restrict__ sub_off,
@@ -513,10 +513,11 @@ __device__ __forceinline__ void team_member(const SolveArgs &a, const TeamArgs &
     // order (16 bits), and a row's state in its thread's registers.  The iterations then
     // touch global memory for what crosses the barriers only, where the general form's
     // chain of each sweep went through L2 four to six times.  Members of a team choose it
-    // independently.  us per iteration, general -> compact: 9241 buses, 1 case 10.7 -> 8.6,
-    // 16 cases 13.5 -> 9.7; 3000 buses, 64 cases 12.5 -> 9.5.  (With more rows per thread,
-    // state in memory, it gained nothing: 48 grids 25.4 -> 26.2.  The gathers of a group
-    // issued together spill 118 registers more: 11.7.)
+    // independently.  us per iteration, general form with the arithmetic before -> this:
+    // 9241 buses, 1 case 11.9 -> 7.9, 16 cases 14.1 -> 8.2; 3000 buses, 64 cases 13.1 -> 8.0
+    // (the arithmetic alone took 1 case to 10.7).  With more rows per thread, state in
+    // memory, it gained nothing (48 grids 25.4 -> 26.2); the gathers of a group issued
+    // together spill 118 registers more and are a third slower.
     const int R = rhi - rlo;
     const int xc = R + max(n_halo, 0);
     const int sl0 = slice0 + rlo / kWave;
