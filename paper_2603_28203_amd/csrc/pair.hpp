@@ -123,7 +123,7 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
 
     const int64_t cb = (int64_t)c * a.ld;
     const int64_t sb = (int64_t)c * a.s_ld;
-    double *__restrict__ Qg = kept_values(a.scratch, cb + lo);  // Im(V conj(I)) by local row (see q_lds)
+    double *__restrict__ Qg = kept_values(a.scratch + cb, lo);  // Im(V conj(I)) of every row (see q_lds)
     double2 *__restrict__ P0 = a.scratch + a.st_stride + cb;
     double2 *__restrict__ P1 = a.scratch + 2 * a.st_stride + cb;
     double2 *__restrict__ P2 = a.scratch + 3 * a.st_stride + cb;
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                     if (q_lds) {
                         if (tk == kPV) Ql[pv_slot(il, tk)] = qv;
                     } else {
-                        Qg[il] = qv;
+                        Qg[i] = qv;
                     }
                     w[j] = cmulc(av, v);
                 }
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(NT) void team_solve_pair_kernel(SolveArgs a) {
                     double sn0, cs0;
                     fast_sincos(vai, sn0, cs0);
                     double qv = 0.0;
-                    if (!q_lds) qv = Qg[il];
+                    if (!q_lds) qv = Qg[i];
                     else if (tk == kPV) qv = Ql[pv_slot(il, tk)];
                     const SeedTerm g = gradient_of_row(X[il], h, vmi, cs0, sn0, sp, qv, half_m, tk == kPQ);
                     double mv = p1.x, ma = p1.y, sv = p2.x, sa = p2.y;

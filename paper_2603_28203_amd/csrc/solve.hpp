@@ -1112,13 +1112,13 @@ __device__ __forceinline__ double2 residual_of_row(double2 v, double2 i, double2
     return make_double2(fma(v.x, i.x, fma(v.y, i.y, -s.x)), fma(v.y, i.x, fma(-v.x, i.y, -s.y)));
 }
 
-// Where an item whose first row is entry `row` of a complex scratch array keeps one
-// double per row of its own: in the first half of its own rows' entries, so that items
-// of one call that run on different kernels at the same time never share memory,
-// however each of them uses its entries (an index of 8 B per row over the whole array
-// would reach into the entries of other items).
-__device__ __forceinline__ double *kept_values(double2 *scratch, int64_t row) {
-    return reinterpret_cast<double *>(scratch + row);
+// Where an item whose rows begin at lo keeps one double per row in its case's part of a
+// complex scratch array, indexed by row: in the first half of its own rows' entries, so
+// that items of one call that run on different kernels at the same time never share
+// memory, however each of them uses its entries (indexed from 0 over the case's 8-byte
+// words, the values would reach into the entries of other items).
+__device__ __forceinline__ double *kept_values(double2 *scratch, int lo) {
+    return reinterpret_cast<double *>(scratch) + lo;
 }
 
 // The gradient of one row from w = a conj(V) and h = (Y w), without I.  With
@@ -1209,7 +1209,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
     double *__restrict__ ma_c = a.st + a.st_stride + cb;
     double *__restrict__ sv_c = a.st + 2 * a.st_stride + cb;
     double *__restrict__ sa_c = a.st + 3 * a.st_stride + cb;
-    double *__restrict__ Qg = kept_values(a.scratch, cb + lo);  // Im(V conj(I)) of the A/W sweep, by local row
+    double *__restrict__ Qg = kept_values(a.scratch + cb, lo);  // Im(V conj(I)) of the A/W sweep
     const double2 *__restrict__ Sc = a.s_spec + sb;
     const int32_t *__restrict__ swidth = a.sell.width;
     const int32_t *__restrict__ sstart = a.sell.start;
@@ -1270,7 +1270,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     lsum += rP * rP + rQ * rQ;
                     lmax = fmax(lmax, fmax(fabs(rP), fabs(rQ)));
                     const double2 av = make_double2(two_over_m * rP, two_over_m * rQ);
-                    Qg[il] = qv;
+                    Qg[i] = qv;
                     w[j] = cmulc(av, v);
                 }
             }
@@ -1309,7 +1309,7 @@ __global__ __launch_bounds__(NT) void team_solve_band_kernel(SolveArgs a) {
                     const int i = lo + il;
                     // every global load of this bus first, so that they overlap the gather
                     const int8_t tk = btp[i];
-                    const double qv = Qg[il];
+                    const double qv = Qg[i];
                     const double2 sp = Sc[i];
                     double vmi = vm_c[i], vai = va_c[i];
                     const double mv0 = mv_c[i], sv0 = sv_c[i], ma0 = ma_c[i], sa0 = sa_c[i];

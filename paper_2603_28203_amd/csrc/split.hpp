@@ -156,7 +156,7 @@ __global__ __launch_bounds__(NT) void team_solve_split_kernel(SolveArgs a, Split
     double *__restrict__ ma_c = a.st + a.st_stride + cb;
     double *__restrict__ sv_c = a.st + 2 * a.st_stride + cb;
     double *__restrict__ sa_c = a.st + 3 * a.st_stride + cb;
-    double *__restrict__ Qg = kept_values(p.Qg, cb);
+    double *__restrict__ Qg = kept_values(p.Qg + cb, 0);
     double2 *__restrict__ Wg = p.Wg + cb;
     const double2 *__restrict__ Sc = a.s_spec + (int64_t)c * a.s_ld;
     const int32_t *__restrict__ swidth = a.sell.width;
